@@ -198,7 +198,8 @@ bool valid_nr(int n, int nr)
 // ---------------------------------------------------------------------------
 // Workspace layout (every region 256-byte aligned).
 struct Ws {
-    CgState* st = nullptr;
+    CgState* st = nullptr;  // the host's copy of the CG scalars
+    CgState* cs = nullptr;  // the two copies of a poll block
     double* red = nullptr;
     uint32_t* cnt = nullptr;
     size_t cnt_bytes = 0;
@@ -238,8 +239,9 @@ size_t ws_layout(const Lat& lat, int n, int mode, int kind, char* base, Ws* w)
     const size_t f32 = (size_t)lat.Vh * 3 * n * sizeof(f2);
     const size_t maxblocks = (size_t)lat.Vh * 8 / 64 + 1;  // block >= 64 threads, <= 8 per site
     w->st = (CgState*)take(sizeof(CgState));
+    w->cs = (CgState*)take(2 * sizeof(CgState));
     w->red = (double*)take(red_doubles(maxblocks) * sizeof(double));
-    w->cnt_bytes = align256(red_counters(maxblocks) * sizeof(uint32_t));
+    w->cnt_bytes = kRedCounters * sizeof(uint32_t);
     w->cnt = (uint32_t*)take(w->cnt_bytes);
     w->r64 = (d2*)take(f64);
     w->t64 = (d2*)take(f64);
@@ -272,6 +274,25 @@ size_t ws_layout(const Lat& lat, int n, int mode, int kind, char* base, Ws* w)
     return off;
 }
 
+// Where the sum `slot` of a grid of nblk work-groups goes, and as its consumer
+// sees it.
+SumOut sum_out(const Ws& w, int slot, int nblk, int n)
+{
+    return SumOut{w.red + (size_t)slot * kSumDoubles, w.red + (size_t)SUM_SLOTS * kSumDoubles, w.cnt,
+                  sum_group(nblk, n)};
+}
+SumIn sum_in(const Ws& w, int slot, int nblk, int n)
+{
+    return SumIn{w.red + (size_t)slot * kSumDoubles, sum_row_count(nblk, n)};
+}
+// work-groups of a Dslash (or site-tiled p-update) launch
+int tile_blocks(const Lat& lat, int n, int nr, int bs)
+{
+    const long threads = (long)lat.Vh * (n / nr);
+    return (int)((threads + bs - 1) / bs);
+}
+int tile_blocks(const Lat& lat, int n, const Tile& t) { return tile_blocks(lat, n, t.nr, t.bs); }
+
 // ---------------------------------------------------------------------------
 // Packed link access.
 template <typename T>
@@ -284,16 +305,18 @@ const cplx<T>* link_block(const void* packed, int Vh, int nk, int parity)
 
 // cm: colour-major fields (every solver launch); false only for the plain
 // Dslash on canonical site-major fields.
-hipError_t launch_ds(int epi, int n, int nk, const Tile& t, const DslashArgs<double>& a,
-                     hipStream_t s, bool cm = true)
+hipError_t launch_ds(int epi, int n, int nk, const Tile& t, DslashArgs<double> a, hipStream_t s,
+                     bool cm = true)
 {
     (void)nk;
+    a.sum.group = sum_group(tile_blocks(a.lat, n, t), n);
     return launch_dslash_f64(epi, n, t, a, s, cm);
 }
 
-hipError_t launch_ds(int epi, int n, int nk, const Tile& t, const DslashArgs<float>& a,
-                     hipStream_t s, bool cm = true)
+hipError_t launch_ds(int epi, int n, int nk, const Tile& t, DslashArgs<float> a, hipStream_t s,
+                     bool cm = true)
 {
+    a.sum.group = sum_group(tile_blocks(a.lat, n, t), n);
     return launch_dslash_f32(epi, nk, n, t, a, s, cm);
 }
 
@@ -306,6 +329,11 @@ Tile unstaged(const Tile& t)
 {
     if (t.rows == 0 && t.bs <= kMaxBlock) return t;
     return Tile{t.nr, 128, t.remap, 0};
+}
+
+int pup_blocks(const Lat& lat, int n, const Tile& t)
+{
+    return pupdate_flat_ok(n) ? pupdate_flat_blocks(n, lat.Vh) : tile_blocks(lat, n, unstaged(t));
 }
 
 hipError_t launch_pup(int n, const Tile& t, const PupdateArgs<double>& a, hipStream_t s)
@@ -557,8 +585,7 @@ struct Engine {
         a.links = link_block<double>(q.links64, q.lat.Vh, HISQ_NAIK_FULL, parity);
         a.mass4 = q.m4;
         a.state = q.w.st;
-        a.red = q.w.red;
-        a.cnt = q.w.cnt;
+        a.sum = sum_out(q.w, SUM_RR, 1, q.n);
         return a;
     }
 
@@ -575,11 +602,19 @@ struct Engine {
         c.b = q.b;
         c.xh = q.x;
         HIP_TRY(launch_ds(EPI_RESID, q.n, HISQ_NAIK_FULL, q.t64, c, s));
+        HIP_TRY(launch_sum_final(sum_in(q.w, SUM_RR, tile_blocks(q.lat, q.n, q.t64), q.n), q.n, 1.0,
+                                 q.w.st->rr_true, s));
         return HISQ_OK;
     }
 
+    // Copy of q's CG scalars number j: the host's, then the two of a poll block.
+    static CgState* state_copy(const Prob& q, int j) { return j == 0 ? q.w.st : q.w.cs + (j - 1); }
+
+    // The arguments of the three kernels of an iteration in `phase` (phase_of),
+    // for grids of nb1, nb2 and nb3 work-groups.
     template <typename T>
-    void iter_args(const Prob& q, PupdateArgs<T>& k1, DslashArgs<T>& k2, DslashArgs<T>& k3) const
+    void iter_args(const Prob& q, PupdateArgs<T>& k1, DslashArgs<T>& k2, DslashArgs<T>& k3, int phase,
+                   int nb1, int nb2, int nb3) const
     {
         const void* L = std::is_same<T, float>::value ? q.links32 : q.links64;
         const int rr = std::is_same<T, float>::value ? nk : HISQ_NAIK_FULL;
@@ -603,9 +638,11 @@ struct Engine {
         k1.lat = q.lat;
         k1.r = r;
         k1.p = p;
-        k1.state = q.w.st;
-        k1.red = q.w.red;
-        k1.cnt = q.w.cnt;
+        k1.src = state_copy(q, state_of_phase(phase, 0));
+        k1.dst = state_copy(q, state_of_phase(phase, 1));
+        k1.rr = sum_in(q.w, SUM_RR, nb3, q.n);
+        k1.fresh = phase == 0;
+        k1.sum = sum_out(q.w, SUM_PP, nb1, q.n);
         k1.remap = tile.remap;
         k2 = DslashArgs<T>{};
         k2.lat = q.lat;
@@ -615,11 +652,13 @@ struct Engine {
         k2.in = p;
         k2.out = t;
         k2.mass4 = q.m4;
-        k2.state = q.w.st;
-        k2.red = q.w.red;
-        k2.cnt = q.w.cnt;
+        k2.state = k1.dst;
+        k2.sum = sum_out(q.w, SUM_TT, nb2, q.n);
         k2.remap = tile.remap;
         k3 = k2;
+        k3.sum = sum_out(q.w, SUM_RR, nb3, q.n);
+        k3.pp = sum_in(q.w, SUM_PP, nb1, q.n);
+        k3.tt = sum_in(q.w, SUM_TT, nb2, q.n);
         k3.parity = 0;
         k3.links = link_block<T>(L, q.lat.Vh, rr, 0);
         k3.in = t;
@@ -630,14 +669,15 @@ struct Engine {
     }
 
     template <typename T>
-    int emit_single(hipStream_t st, hipEvent_t* evs)
+    int emit_single(hipStream_t st, int phase, hipEvent_t* evs)
     {
         const Prob& q = P[0];
         PupdateArgs<T> k1;
         DslashArgs<T> k2, k3;
-        iter_args<T>(q, k1, k2, k3);
         const Tile& tile = std::is_same<T, float>::value ? q.t32 : q.t64;
         const Tile& tile_e = std::is_same<T, float>::value ? q.t32e : q.t64e;
+        iter_args<T>(q, k1, k2, k3, phase, pup_blocks(q.lat, q.n, tile), tile_blocks(q.lat, q.n, tile),
+                     tile_blocks(q.lat, q.n, tile_e));
         const int rr = std::is_same<T, float>::value ? nk : HISQ_NAIK_FULL;
         if (evs) HIP_TRY(hipEventRecord(evs[0], st));
         HIP_TRY(launch_pup(q.n, tile, k1, st));
@@ -650,22 +690,22 @@ struct Engine {
     }
 
     template <typename T>
-    int emit_batched(hipStream_t st, hipEvent_t* evs)
+    int emit_batched(hipStream_t st, int phase, hipEvent_t* evs)
     {
         const BatchTable<T>* tab = reinterpret_cast<const BatchTable<T>*>(table);
         if (evs) HIP_TRY(hipEventRecord(evs[0], st));
         if constexpr (std::is_same<T, float>::value) {
-            HIP_TRY(launch_pupdate_batched_f32(tab, batch_blocks, batch_bs, st));
+            HIP_TRY(launch_pupdate_batched_f32(tab, batch_blocks, batch_bs, phase, st));
             if (evs) HIP_TRY(hipEventRecord(evs[1], st));
-            HIP_TRY(launch_dslash_batched_f32(EPI_NORM, nk, tab, batch_blocks, batch_bs, st));
+            HIP_TRY(launch_dslash_batched_f32(EPI_NORM, nk, tab, batch_blocks, batch_bs, phase, st));
             if (evs) HIP_TRY(hipEventRecord(evs[2], st));
-            HIP_TRY(launch_dslash_batched_f32(EPI_CG, nk, tab, batch_blocks, batch_bs, st));
+            HIP_TRY(launch_dslash_batched_f32(EPI_CG, nk, tab, batch_blocks, batch_bs, phase, st));
         } else {
-            HIP_TRY(launch_pupdate_batched_f64(tab, batch_blocks, batch_bs, st));
+            HIP_TRY(launch_pupdate_batched_f64(tab, batch_blocks, batch_bs, phase, st));
             if (evs) HIP_TRY(hipEventRecord(evs[1], st));
-            HIP_TRY(launch_dslash_batched_f64(EPI_NORM, tab, batch_blocks, batch_bs, st));
+            HIP_TRY(launch_dslash_batched_f64(EPI_NORM, tab, batch_blocks, batch_bs, phase, st));
             if (evs) HIP_TRY(hipEventRecord(evs[2], st));
-            HIP_TRY(launch_dslash_batched_f64(EPI_CG, tab, batch_blocks, batch_bs, st));
+            HIP_TRY(launch_dslash_batched_f64(EPI_CG, tab, batch_blocks, batch_bs, phase, st));
         }
         if (evs) HIP_TRY(hipEventRecord(evs[3], st));
         return HISQ_OK;
@@ -675,21 +715,34 @@ struct Engine {
     {
         for (int j = 0; j < iters; ++j) {
             hipEvent_t* evs = with_events ? &ev[4 * j] : nullptr;
+            const int ph = phase_of(j);
             int rc;
             if (P.size() == 1)
-                rc = mixed ? emit_single<float>(st, evs) : emit_single<double>(st, evs);
+                rc = mixed ? emit_single<float>(st, ph, evs) : emit_single<double>(st, ph, evs);
             else
-                rc = mixed ? emit_batched<float>(st, evs) : emit_batched<double>(st, evs);
+                rc = mixed ? emit_batched<float>(st, ph, evs) : emit_batched<double>(st, ph, evs);
             if (rc) return rc;
         }
+        // the last iteration's |r|^2 and scalars into the host's copies
+        FoldArgs f{};
+        const int last = state_of_phase(phase_of(iters - 1), 1);
+        for (size_t j = 0; j < P.size(); ++j) {
+            const Prob& q = P[j];
+            const int nb3 = P.size() > 1 ? tile_blocks(q.lat, q.n, batch_nr(q), batch_bs)
+                                         : tile_blocks(q.lat, q.n, mixed ? q.t32e : q.t64e);
+            f.p[j] = FoldArgs::One{state_copy(q, last), q.w.st, sum_in(q.w, SUM_RR, nb3, q.n), q.n};
+        }
+        HIP_TRY(launch_fold(f, (int)P.size(), st));
         return HISQ_OK;
     }
+
+    static int batch_nr(const Prob& q) { return batched_nr_ok(q.n, q.bnr) ? q.bnr : q.n; }
 
     // Batch table over the problems `which` (all if empty), each with its own
     // rhs tile bnr, for work-groups of bs threads; uploads it and sets
     // batch_blocks.
     template <typename T>
-    int upload_table(void* host_buf, const std::vector<int>& which, int bs)
+    int upload_table(void* host_buf, const std::vector<int>& which, int bs, bool tuning = false)
     {
         BatchTable<T>* tab = reinterpret_cast<BatchTable<T>*>(host_buf);
         std::memset(tab, 0, sizeof(*tab));
@@ -698,15 +751,16 @@ struct Engine {
         for (int jj = 0; jj < np; ++jj) {
             const Prob& q = P[which.empty() ? jj : which[jj]];
             BatchProb<T>& bp = tab->p[jj];
-            iter_args<T>(q, bp.k1, bp.k2, bp.k3);
             bp.n = q.n;
-            bp.nr = batched_nr_ok(q.n, q.bnr) ? q.bnr : q.n;
+            bp.nr = batch_nr(q);
+            bp.nblocks = tile_blocks(q.lat, q.n, bp.nr, bs);
+            iter_args<T>(q, bp.k1, bp.k2, bp.k3, 0, bp.nblocks, bp.nblocks, bp.nblocks);
+            // the tuner times the Dslash kernels on the host's (frozen) copy alone
+            for (int c = 0; c < 3; ++c) bp.state[c] = state_copy(q, tuning ? 0 : c);
             // XCD-owned z-chunks where the problem's tiles allow, else one
             // contiguous slab per XCD
             const int G = q.n / bp.nr;
             bp.k1.remap = bp.k2.remap = bp.k3.remap = t_order_ok(q.lat, G, bs, 3) ? 3 : 1;
-            const long threads = (long)q.lat.Vh * G;
-            bp.nblocks = (int)((threads + bs - 1) / bs);
             bp.k1.ntiles = bp.k2.ntiles = bp.k3.ntiles = bp.nblocks;
             bp.block_start = start;
             start += bp.nblocks;
@@ -777,7 +831,8 @@ struct Engine {
 // (states armed and frozen by the caller), work-groups of bs threads.
 int Engine::batched_time(void* host_buf, const std::vector<int>& which, int bs, float* ms)
 {
-    int rc = mixed ? upload_table<float>(host_buf, which, bs) : upload_table<double>(host_buf, which, bs);
+    int rc = mixed ? upload_table<float>(host_buf, which, bs, true)
+                   : upload_table<double>(host_buf, which, bs, true);
     if (rc) return rc;
     hipEvent_t tev[2] = {nullptr, nullptr};
     auto release = on_scope_exit([&] { destroy_events(tev, 2); });
@@ -787,12 +842,12 @@ int Engine::batched_time(void* host_buf, const std::vector<int>& which, int bs, 
     auto pair = [&]() -> int {
         if (mixed) {
             const auto* tab = reinterpret_cast<const BatchTable<float>*>(table);
-            HIP_TRY(launch_dslash_batched_f32(EPI_NORM, nk, tab, batch_blocks, bs, s));
-            HIP_TRY(launch_dslash_batched_f32(EPI_CG, nk, tab, batch_blocks, bs, s));
+            HIP_TRY(launch_dslash_batched_f32(EPI_NORM, nk, tab, batch_blocks, bs, 0, s));
+            HIP_TRY(launch_dslash_batched_f32(EPI_CG, nk, tab, batch_blocks, bs, 0, s));
         } else {
             const auto* tab = reinterpret_cast<const BatchTable<double>*>(table);
-            HIP_TRY(launch_dslash_batched_f64(EPI_NORM, tab, batch_blocks, bs, s));
-            HIP_TRY(launch_dslash_batched_f64(EPI_CG, tab, batch_blocks, bs, s));
+            HIP_TRY(launch_dslash_batched_f64(EPI_NORM, tab, batch_blocks, bs, 0, s));
+            HIP_TRY(launch_dslash_batched_f64(EPI_CG, tab, batch_blocks, bs, 0, s));
         }
         return HISQ_OK;
     };
@@ -892,7 +947,7 @@ int Engine::setup(CgState* host)
             HIP_TRY(launch_layout(q.ux, q.w.xc, q.lat.Vh, q.n, true, s));
         else
             HIP_TRY(launch_zero(q.x, nc * sizeof(d2), s));
-        HIP_TRY(launch_norm2_f64(q.b, q.lat.Vh, q.n, q.w.st->aux, q.w.red, q.w.cnt, s));
+        HIP_TRY(launch_norm2_f64(q.b, q.lat.Vh, q.n, q.w.st->aux, sum_out(q.w, SUM_RR, 1, q.n), s));
         if ((rc = true_residual(q))) return rc;
         if (mixed) {
             HIP_TRY(launch_to_f32_sel(q.w.r64, q.w.r32, nc, q.n, q.w.st, s));
@@ -1127,8 +1182,7 @@ int Engine::run(hisq_info* infos)
             p32.out = q.w.t32;
             p32.mass4 = q.m4;
             p32.state = q.w.st;
-            p32.red = q.w.red;
-            p32.cnt = q.w.cnt;
+            p32.sum = sum_out(q.w, SUM_TT, 1, q.n);
             if ((rc = get_tile(q.lat, q.n, HISQ_PREC_F32, nk, p32, s, &q.t32, EPI_NORM))) return rc;
         }
         // the D_eo kernel with the CG epilogue, timed on the iteration's own
@@ -1142,12 +1196,14 @@ int Engine::run(hisq_info* infos)
             if (mixed) {
                 PupdateArgs<float> k1;
                 DslashArgs<float> k2, k3;
-                iter_args<float>(q, k1, k2, k3);
+                iter_args<float>(q, k1, k2, k3, 0, 1, 1, 1);
+                k3.state = q.w.st;
                 if ((rc = get_tile(q.lat, q.n, HISQ_PREC_F32, nk, k3, s, &q.t32e, EPI_CG))) return rc;
             } else {
                 PupdateArgs<double> k1;
                 DslashArgs<double> k2, k3;
-                iter_args<double>(q, k1, k2, k3);
+                iter_args<double>(q, k1, k2, k3, 0, 1, 1, 1);
+                k3.state = q.w.st;
                 if ((rc = get_tile(q.lat, q.n, HISQ_PREC_F64, HISQ_NAIK_FULL, k3, s, &q.t64e, EPI_CG)))
                     return rc;
             }
@@ -1678,7 +1734,7 @@ int hisq_cg_solve_backward(const hisq_geom* g, double mass, int nrhs, const hisq
                          reinterpret_cast<d2*>(grad_N), s));
     if (p->profile) HIP_TRY(hipEventRecord(fe[1], s));
     HIP_TRY(launch_redot(y, reinterpret_cast<const d2*>(x_e), lat.Vh, nrhs, -8.0 * mass, grad_m,
-                         w.red, w.cnt, s));
+                         sum_out(w, SUM_RR, 1, 1), s));
     HIP_TRY(hipStreamSynchronize(s));
     if (p->profile) {
         float ms = 0;

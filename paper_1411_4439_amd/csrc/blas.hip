@@ -4,28 +4,41 @@
 
 namespace hisq {
 
+// The scalars that open an iteration, as this thread's rhs g*NR + k needs them;
+// false if no rhs of the bundle is active.
+template <int NRHS, int NR, typename T>
+__device__ __forceinline__ bool cg_begin(const CgState* src, CgState* dst, const SumIn& rr, int fresh,
+                                         bool writer, int g, bool (&act)[NR], T (&beta)[NR])
+{
+    bool on;
+    double b;
+    cg_scalars<NRHS>(src, dst, rr, fresh, writer, on, b);
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+        act[k] = __shfl((int)on, g * NR + k, 64) != 0;
+        beta[k] = __shfl((T)b, g * NR + k, 64);
+    }
+    return __any(on);
+}
+
 // ---------------------------------------------------------------------------
-// p = r + beta_k p for every active rhs k; |p_k|^2 summed in FP64 -> pp[k].
+// p = r + beta_k p for every active rhs k; |p_k|^2 summed in FP64.
 // (site-tiled form, colour-major fields: bundles the streaming form does not cover)
 template <typename T, int NRHS, int NR>
-__device__ __forceinline__ void pupdate_tile(const PupdateArgs<T>& a, int tile, int nblk, int bid)
+__device__ __forceinline__ void pupdate_tile(const PupdateArgs<T>& a, const CgState* src, CgState* dst,
+                                             int fresh, int tile, int nblk, int bid)
 {
     using C = cplx<T>;
     constexpr int G = NRHS / NR;
     const int g = threadIdx.x % G;
-    bool any_prob = false;
-#pragma unroll
-    for (int k = 0; k < NRHS; ++k) any_prob = any_prob || (a.state->active[k] != 0);
-    if (!any_prob) return;  // every rhs converged: nothing to do, nothing to reduce
-
     bool act[NR];
     T beta[NR];
+    if (!cg_begin<NRHS, NR>(src, dst, a.rr, fresh, bid == 0 && threadIdx.x < 64, g, act, beta))
+        return;  // every rhs converged: nothing to do, nothing to reduce
     bool any_act = false;
     double part[NR];
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
-        act[k] = a.state->active[g * NR + k] != 0;
-        beta[k] = (T)a.state->beta[g * NR + k];
         any_act = any_act || act[k];
         part[k] = 0.0;
     }
@@ -52,26 +65,23 @@ __device__ __forceinline__ void pupdate_tile(const PupdateArgs<T>& a, int tile, 
         }
     }
     // partials first, then the stores (converged rhs are not written)
-    const bool last = grid_reduce_post<NRHS, NR>(part, a.red, a.cnt, nblk, bid);
+    const bool last = sum_post<NRHS, NR>(part, a.sum, nblk, bid);
     if (work) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) store_rhs_on<NR>(a.p + base + Lay::colour(c, a.lat.Vh), pv[c], act);
     }
-    double total;
-    if (last && grid_reduce_finish<NRHS>(a.red, a.cnt, nblk, bid, &total)) {
-        if (threadIdx.x < NRHS && !a.state->frozen) a.state->pp[threadIdx.x] = total;
-    }
+    if (last) sum_finish<NRHS>(a.sum, nblk, bid);
 }
 
 template <typename T, int NRHS, int NR>
 __global__ __launch_bounds__(kMaxBlock) void k_pupdate(const PupdateArgs<T> a)
 {
-    pupdate_tile<T, NRHS, NR>(a, tile_of_block(blockIdx.x, gridDim.x, a.remap, a.lat, (int)blockDim.x / (NRHS / NR)), gridDim.x,
+    pupdate_tile<T, NRHS, NR>(a, a.src, a.dst, a.fresh, tile_of_block(blockIdx.x, gridDim.x, a.remap, a.lat, (int)blockDim.x / (NRHS / NR)), gridDim.x,
                               blockIdx.x);
 }
 
 template <typename T>
-__global__ __launch_bounds__(kMaxBlock) void k_pupdate_batched(const BatchTable<T>* __restrict__ tab)
+__global__ __launch_bounds__(kMaxBlock) void k_pupdate_batched(const BatchTable<T>* __restrict__ tab, int phase)
 {
     int q = 0;
     for (int j = 1; j < tab->nprob; ++j)
@@ -81,19 +91,22 @@ __global__ __launch_bounds__(kMaxBlock) void k_pupdate_batched(const BatchTable<
     if (bid >= bp.nblocks) return;
     const int nb = bp.nblocks;
     const int tile = tile_of_block(bid, nb, bp.k1.remap, bp.k1.lat, (int)blockDim.x / (bp.n / bp.nr));
+    const CgState* src = bp.state[state_of_phase(phase, 0)];
+    CgState* dst = bp.state[state_of_phase(phase, 1)];
+    const int fresh = phase == 0;
     switch (bp.n * 16 + bp.nr) {
-    case 1 * 16 + 1: pupdate_tile<T, 1, 1>(bp.k1, tile, nb, bid); break;
-    case 2 * 16 + 2: pupdate_tile<T, 2, 2>(bp.k1, tile, nb, bid); break;
-    case 2 * 16 + 1: pupdate_tile<T, 2, 1>(bp.k1, tile, nb, bid); break;
-    case 3 * 16 + 3: pupdate_tile<T, 3, 3>(bp.k1, tile, nb, bid); break;
-    case 4 * 16 + 4: pupdate_tile<T, 4, 4>(bp.k1, tile, nb, bid); break;
-    case 4 * 16 + 2: pupdate_tile<T, 4, 2>(bp.k1, tile, nb, bid); break;
-    case 5 * 16 + 5: pupdate_tile<T, 5, 5>(bp.k1, tile, nb, bid); break;
-    case 6 * 16 + 6: pupdate_tile<T, 6, 6>(bp.k1, tile, nb, bid); break;
-    case 6 * 16 + 3: pupdate_tile<T, 6, 3>(bp.k1, tile, nb, bid); break;
-    case 7 * 16 + 7: pupdate_tile<T, 7, 7>(bp.k1, tile, nb, bid); break;
-    case 8 * 16 + 8: pupdate_tile<T, 8, 8>(bp.k1, tile, nb, bid); break;
-    case 8 * 16 + 4: pupdate_tile<T, 8, 4>(bp.k1, tile, nb, bid); break;
+    case 1 * 16 + 1: pupdate_tile<T, 1, 1>(bp.k1, src, dst, fresh, tile, nb, bid); break;
+    case 2 * 16 + 2: pupdate_tile<T, 2, 2>(bp.k1, src, dst, fresh, tile, nb, bid); break;
+    case 2 * 16 + 1: pupdate_tile<T, 2, 1>(bp.k1, src, dst, fresh, tile, nb, bid); break;
+    case 3 * 16 + 3: pupdate_tile<T, 3, 3>(bp.k1, src, dst, fresh, tile, nb, bid); break;
+    case 4 * 16 + 4: pupdate_tile<T, 4, 4>(bp.k1, src, dst, fresh, tile, nb, bid); break;
+    case 4 * 16 + 2: pupdate_tile<T, 4, 2>(bp.k1, src, dst, fresh, tile, nb, bid); break;
+    case 5 * 16 + 5: pupdate_tile<T, 5, 5>(bp.k1, src, dst, fresh, tile, nb, bid); break;
+    case 6 * 16 + 6: pupdate_tile<T, 6, 6>(bp.k1, src, dst, fresh, tile, nb, bid); break;
+    case 6 * 16 + 3: pupdate_tile<T, 6, 3>(bp.k1, src, dst, fresh, tile, nb, bid); break;
+    case 7 * 16 + 7: pupdate_tile<T, 7, 7>(bp.k1, src, dst, fresh, tile, nb, bid); break;
+    case 8 * 16 + 8: pupdate_tile<T, 8, 8>(bp.k1, src, dst, fresh, tile, nb, bid); break;
+    case 8 * 16 + 4: pupdate_tile<T, 8, 4>(bp.k1, src, dst, fresh, tile, nb, bid); break;
     default: break;
     }
 }
@@ -108,21 +121,17 @@ __global__ __launch_bounds__(kMaxBlock) void k_pupdate_flat(const PupdateArgs<T>
 {
     using C = cplx<T>;
     constexpr int G = NRHS / NRT;
-    bool any_prob = false;
-#pragma unroll
-    for (int k = 0; k < NRHS; ++k) any_prob = any_prob || (a.state->active[k] != 0);
-    if (!any_prob) return;
     const long tid = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const long stride = (long)gridDim.x * blockDim.x;  // a multiple of 64, hence of G
     const int g = (int)(tid % G);
     bool act[NRT];
     T beta[NRT];
+    if (!cg_begin<NRHS, NRT>(a.src, a.dst, a.rr, a.fresh, blockIdx.x == 0 && threadIdx.x < 64, g, act, beta))
+        return;
     double part[NRT];
     bool any_act = false;
 #pragma unroll
     for (int k = 0; k < NRT; ++k) {
-        act[k] = a.state->active[g * NRT + k] != 0;
-        beta[k] = (T)a.state->beta[g * NRT + k];
         any_act = any_act || act[k];
         part[k] = 0.0;
     }
@@ -140,22 +149,29 @@ __global__ __launch_bounds__(kMaxBlock) void k_pupdate_flat(const PupdateArgs<T>
             store_rhs_on<NRT>(a.p + j * NRT, pv, act);
         }
     }
-    double total;
-    if (grid_reduce_rhs<NRHS, NRT>(part, a.red, a.cnt, gridDim.x, blockIdx.x, &total)) {
-        if (threadIdx.x < NRHS && !a.state->frozen) a.state->pp[threadIdx.x] = total;
-    }
+    if (sum_post<NRHS, NRT>(part, a.sum, gridDim.x, blockIdx.x))
+        sum_finish<NRHS>(a.sum, gridDim.x, blockIdx.x);
 }
 
 constexpr int kFlatMaxBlocks = 2048;
 
-template <typename T, int NRHS, int NRT>
+// complex numbers per thread and step
+static constexpr int flat_chunk(int nrhs) { return nrhs >= 2 ? 2 : 1; }
+
+int pupdate_flat_blocks(int nrhs, int Vh)
+{
+    const long nchunks = (long)Vh * 3 * nrhs / flat_chunk(nrhs);
+    const long blocks = (nchunks + 255) / 256;
+    return (int)(blocks > kFlatMaxBlocks ? kFlatMaxBlocks : blocks);
+}
+
+template <typename T, int NRHS>
 static hipError_t go_flat(PupdateArgs<T> a, hipStream_t s)
 {
+    constexpr int NRT = flat_chunk(NRHS);
     const long nchunks = (long)a.lat.Vh * 3 * NRHS / NRT;
-    const int bs = 256;
-    long blocks = (nchunks + bs - 1) / bs;
-    if (blocks > kFlatMaxBlocks) blocks = kFlatMaxBlocks;
-    hipLaunchKernelGGL((k_pupdate_flat<T, NRHS, NRT>), dim3((int)blocks), dim3(bs), 0, s, a, nchunks);
+    const int blocks = pupdate_flat_blocks(NRHS, a.lat.Vh);
+    hipLaunchKernelGGL((k_pupdate_flat<T, NRHS, NRT>), dim3(blocks), dim3(256), 0, s, a, nchunks);
     return hipGetLastError();
 }
 
@@ -163,10 +179,10 @@ template <typename T>
 static hipError_t launch_flat(int nrhs, const PupdateArgs<T>& a, hipStream_t s)
 {
     switch (nrhs) {
-    case 1: return go_flat<T, 1, 1>(a, s);
-    case 2: return go_flat<T, 2, 2>(a, s);
-    case 4: return go_flat<T, 4, 2>(a, s);
-    case 8: return go_flat<T, 8, 2>(a, s);
+    case 1: return go_flat<T, 1>(a, s);
+    case 2: return go_flat<T, 2>(a, s);
+    case 4: return go_flat<T, 4>(a, s);
+    case 8: return go_flat<T, 8>(a, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -182,18 +198,18 @@ hipError_t launch_pupdate_flat_f32(int nrhs, const PupdateArgs<float>& a, hipStr
 }
 
 hipError_t launch_pupdate_batched_f64(const BatchTable<double>* tab, int total_blocks, int bs,
-                                      hipStream_t s)
+                                      int phase, hipStream_t s)
 {
     if (bs < 64 || bs > kMaxBlock || bs % 64 != 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pupdate_batched<double>, dim3(total_blocks), dim3(bs), 0, s, tab);
+    hipLaunchKernelGGL(k_pupdate_batched<double>, dim3(total_blocks), dim3(bs), 0, s, tab, phase);
     return hipGetLastError();
 }
 
 hipError_t launch_pupdate_batched_f32(const BatchTable<float>* tab, int total_blocks, int bs,
-                                      hipStream_t s)
+                                      int phase, hipStream_t s)
 {
     if (bs < 64 || bs > kMaxBlock || bs % 64 != 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pupdate_batched<float>, dim3(total_blocks), dim3(bs), 0, s, tab);
+    hipLaunchKernelGGL(k_pupdate_batched<float>, dim3(total_blocks), dim3(bs), 0, s, tab, phase);
     return hipGetLastError();
 }
 
@@ -287,6 +303,50 @@ __global__ void k_state_reset(CgState* st, int nrhs, int active)
 hipError_t launch_state_reset(CgState* st, int nrhs, int active, hipStream_t s)
 {
     hipLaunchKernelGGL(k_state_reset, dim3(1), dim3(64), 0, s, st, nrhs, active);
+    return hipGetLastError();
+}
+
+// One wave per problem: the end of a poll block.
+template <int NP>
+__device__ __forceinline__ void fold_one(const FoldArgs::One& f)
+{
+    bool act;
+    double beta;
+    cg_scalars<NP>(f.src, f.dst, f.rr, 0, true, act, beta);
+}
+
+__global__ void k_fold(FoldArgs a)
+{
+    const FoldArgs::One& f = a.p[blockIdx.x];
+    switch (sum_stride(f.nrhs)) {
+    case 1: fold_one<1>(f); break;
+    case 2: fold_one<2>(f); break;
+    case 4: fold_one<4>(f); break;
+    default: fold_one<8>(f); break;
+    }
+}
+
+hipError_t launch_fold(const FoldArgs& a, int nprob, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_fold, dim3(nprob), dim3(64), 0, s, a);
+    return hipGetLastError();
+}
+
+template <int NP>
+__global__ void k_sum_final(SumIn in, int nrhs, double scale, double* out)
+{
+    const double t = sum_rows<NP>(in);
+    if ((int)threadIdx.x < nrhs) out[threadIdx.x] = scale * t;
+}
+
+hipError_t launch_sum_final(SumIn in, int nrhs, double scale, double* out, hipStream_t s)
+{
+    switch (sum_stride(nrhs)) {
+    case 1: hipLaunchKernelGGL(k_sum_final<1>, dim3(1), dim3(64), 0, s, in, nrhs, scale, out); break;
+    case 2: hipLaunchKernelGGL(k_sum_final<2>, dim3(1), dim3(64), 0, s, in, nrhs, scale, out); break;
+    case 4: hipLaunchKernelGGL(k_sum_final<4>, dim3(1), dim3(64), 0, s, in, nrhs, scale, out); break;
+    default: hipLaunchKernelGGL(k_sum_final<8>, dim3(1), dim3(64), 0, s, in, nrhs, scale, out); break;
+    }
     return hipGetLastError();
 }
 
@@ -400,8 +460,7 @@ hipError_t launch_layout(const d2* src, d2* dst, int Vh, int nrhs, bool to_colou
 // ---------------------------------------------------------------------------
 // Per-rhs |v_k|^2 of an FP64 colour-major half field, one thread per site.
 template <int NRHS>
-__global__ __launch_bounds__(kMaxBlock) void k_norm2(const d2* __restrict__ v, int Vh, double* out,
-                                                     double* red, uint32_t* cnt)
+__global__ __launch_bounds__(kMaxBlock) void k_norm2(const d2* __restrict__ v, int Vh, SumOut o)
 {
     double part[NRHS];
 #pragma unroll
@@ -416,20 +475,18 @@ __global__ __launch_bounds__(kMaxBlock) void k_norm2(const d2* __restrict__ v, i
                 part[k] += e.x * e.x + e.y * e.y;
             }
     }
-    double total;
-    if (grid_reduce_rhs<NRHS, NRHS>(part, red, cnt, gridDim.x, blockIdx.x, &total)) {
-        if (threadIdx.x < NRHS) out[threadIdx.x] = total;
-    }
+    if (sum_post<NRHS, NRHS>(part, o, gridDim.x, blockIdx.x))
+        sum_finish<NRHS>(o, gridDim.x, blockIdx.x);
 }
 
-hipError_t launch_norm2_f64(const d2* v, int Vh, int nrhs, double* out, double* red,
-                            uint32_t* cnt, hipStream_t s)
+hipError_t launch_norm2_f64(const d2* v, int Vh, int nrhs, double* out, SumOut o, hipStream_t s)
 {
     const int bs = 256, grid = (Vh + bs - 1) / bs;
+    o.group = sum_group(grid, nrhs);
     switch (nrhs) {
 #define HISQ_NORM_CASE(N)                                                                   \
     case N:                                                                                 \
-        hipLaunchKernelGGL(k_norm2<N>, dim3(grid), dim3(bs), 0, s, v, Vh, out, red, cnt); \
+        hipLaunchKernelGGL(k_norm2<N>, dim3(grid), dim3(bs), 0, s, v, Vh, o);             \
         break;
         HISQ_NORM_CASE(1)
         HISQ_NORM_CASE(2)
@@ -442,14 +499,15 @@ hipError_t launch_norm2_f64(const d2* v, int Vh, int nrhs, double* out, double* 
 #undef HISQ_NORM_CASE
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_sum_final(SumIn{o.rows, sum_row_count(grid, nrhs)}, nrhs, 1.0, out, s);
 }
 
 // out = scale * sum over sites, colours and rhs of Re(conj(y) x).
 __global__ __launch_bounds__(kMaxBlock) void k_redot(const d2* __restrict__ y,
                                                      const d2* __restrict__ x, int Vh, int nrhs,
-                                                     double scale, double* out, double* red,
-                                                     uint32_t* cnt)
+                                                     SumOut o)
 {
     double part[1] = {0.0};
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -460,18 +518,18 @@ __global__ __launch_bounds__(kMaxBlock) void k_redot(const d2* __restrict__ y,
             part[0] += a.x * b.x + a.y * b.y;
         }
     }
-    double total;
-    if (grid_reduce_rhs<1, 1>(part, red, cnt, gridDim.x, blockIdx.x, &total)) {
-        if (threadIdx.x == 0) *out = scale * total;
-    }
+    if (sum_post<1, 1>(part, o, gridDim.x, blockIdx.x)) sum_finish<1>(o, gridDim.x, blockIdx.x);
 }
 
 hipError_t launch_redot(const d2* y, const d2* x, int Vh, int nrhs, double scale, double* out,
-                        double* red, uint32_t* cnt, hipStream_t s)
+                        SumOut o, hipStream_t s)
 {
     const int bs = 256, grid = (Vh + bs - 1) / bs;
-    hipLaunchKernelGGL(k_redot, dim3(grid), dim3(bs), 0, s, y, x, Vh, nrhs, scale, out, red, cnt);
-    return hipGetLastError();
+    o.group = sum_group(grid, 1);
+    hipLaunchKernelGGL(k_redot, dim3(grid), dim3(bs), 0, s, y, x, Vh, nrhs, o);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_sum_final(SumIn{o.rows, sum_row_count(grid, 1)}, 1, scale, out, s);
 }
 
 // ---------------------------------------------------------------------------

@@ -26,7 +26,7 @@ HISQ_DECL(4, 1, float)
 HISQ_DECL(4, 2, float)
 #undef HISQ_DECL
 #define HISQ_BDECL(P, E, T) \
-    hipError_t launch_dslash_batched_p##P##_e##E(const BatchTable<T>* tab, int total_blocks, int bs, hipStream_t s);
+    hipError_t launch_dslash_batched_p##P##_e##E(const BatchTable<T>* tab, int total_blocks, int bs, int phase, hipStream_t s);
 HISQ_BDECL(0, 1, double)
 HISQ_BDECL(0, 2, double)
 HISQ_BDECL(1, 1, float)
@@ -40,27 +40,27 @@ HISQ_BDECL(4, 2, float)
 #undef HISQ_BDECL
 
 hipError_t launch_dslash_batched_f64(int epi, const BatchTable<double>* tab, int total_blocks,
-                                     int bs, hipStream_t s)
+                                     int bs, int phase, hipStream_t s)
 {
-    if (epi == EPI_NORM) return launch_dslash_batched_p0_e1(tab, total_blocks, bs, s);
-    if (epi == EPI_CG) return launch_dslash_batched_p0_e2(tab, total_blocks, bs, s);
+    if (epi == EPI_NORM) return launch_dslash_batched_p0_e1(tab, total_blocks, bs, phase, s);
+    if (epi == EPI_CG) return launch_dslash_batched_p0_e2(tab, total_blocks, bs, phase, s);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_dslash_batched_f32(int epi, int nk, const BatchTable<float>* tab,
-                                     int total_blocks, int bs, hipStream_t s)
+                                     int total_blocks, int bs, int phase, hipStream_t s)
 {
     if (epi == EPI_NORM) {
-        if (nk == HISQ_NAIK_R14) return launch_dslash_batched_p2_e1(tab, total_blocks, bs, s);
-        if (nk == HISQ_NAIK_R13) return launch_dslash_batched_p3_e1(tab, total_blocks, bs, s);
-        if (nk == HISQ_NAIK_R9) return launch_dslash_batched_p4_e1(tab, total_blocks, bs, s);
-        return launch_dslash_batched_p1_e1(tab, total_blocks, bs, s);
+        if (nk == HISQ_NAIK_R14) return launch_dslash_batched_p2_e1(tab, total_blocks, bs, phase, s);
+        if (nk == HISQ_NAIK_R13) return launch_dslash_batched_p3_e1(tab, total_blocks, bs, phase, s);
+        if (nk == HISQ_NAIK_R9) return launch_dslash_batched_p4_e1(tab, total_blocks, bs, phase, s);
+        return launch_dslash_batched_p1_e1(tab, total_blocks, bs, phase, s);
     }
     if (epi == EPI_CG) {
-        if (nk == HISQ_NAIK_R14) return launch_dslash_batched_p2_e2(tab, total_blocks, bs, s);
-        if (nk == HISQ_NAIK_R13) return launch_dslash_batched_p3_e2(tab, total_blocks, bs, s);
-        if (nk == HISQ_NAIK_R9) return launch_dslash_batched_p4_e2(tab, total_blocks, bs, s);
-        return launch_dslash_batched_p1_e2(tab, total_blocks, bs, s);
+        if (nk == HISQ_NAIK_R14) return launch_dslash_batched_p2_e2(tab, total_blocks, bs, phase, s);
+        if (nk == HISQ_NAIK_R13) return launch_dslash_batched_p3_e2(tab, total_blocks, bs, phase, s);
+        if (nk == HISQ_NAIK_R9) return launch_dslash_batched_p4_e2(tab, total_blocks, bs, phase, s);
+        return launch_dslash_batched_p1_e2(tab, total_blocks, bs, phase, s);
     }
     return hipErrorInvalidValue;
 }

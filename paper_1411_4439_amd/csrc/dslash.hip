@@ -375,43 +375,6 @@ __device__ __forceinline__ void pin_acc(C (&acc)[3][NR])
         for (int k = 0; k < NR; ++k) asm volatile("" ::"v"(acc[c][k].x), "v"(acc[c][k].y));
 }
 
-template <int EPI>
-__device__ __forceinline__ void finish(CgState* st, int k, double tot, double m4)
-{
-    if (st->frozen) return;
-    if constexpr (EPI == EPI_NORM) {
-        // alpha = rr / <p, A p>, with <p, A p> = 4m^2 |p|^2 + |D_oe p|^2 (D_eo^dag = -D_oe)
-        st->tt[k] = tot;
-        if (st->active[k]) {
-            const double den = m4 * st->pp[k] + tot;
-            if (!(den > 0.0) || !finite_d(den)) {
-                st->status[k] = HISQ_BREAKDOWN;
-                st->active[k] = 0;
-                st->alpha[k] = 0.0;
-            } else {
-                st->alpha[k] = st->rr[k] / den;
-            }
-        } else {
-            st->alpha[k] = 0.0;
-        }
-    } else if constexpr (EPI == EPI_CG) {
-        if (st->active[k]) {
-            st->iters[k] += 1;
-            if (!finite_d(tot)) {
-                st->status[k] = HISQ_BREAKDOWN;
-                st->active[k] = 0;
-            } else {
-                st->beta[k] = tot / st->rr[k];
-                st->rr[k] = tot;
-                if (tot > st->rrmax[k]) st->rrmax[k] = tot;
-                if (tot <= st->thresh[k] || st->iters[k] >= st->maxiter) st->active[k] = 0;
-            }
-        }
-    } else if constexpr (EPI == EPI_RESID) {
-        st->rr_true[k] = tot;
-    }
-}
-
 template <typename T>
 __device__ __forceinline__ double norm2c(cplx<T> v)
 {
@@ -422,8 +385,8 @@ __device__ __forceinline__ double norm2c(cplx<T> v)
 // EPI; `tile` is the tile index, the problem's grid has nblk work-groups and
 // this one is number bid (for the reductions).
 template <typename T, int NRHS, int NR, int NK, int EPI, bool CM, bool ST = false>
-__device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, int tile, int nblk, int bid,
-                                            cplx<T>* lds = nullptr)
+__device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* state, int tile,
+                                            int nblk, int bid, cplx<T>* lds = nullptr)
 {
     using C = cplx<T>;
     constexpr int G = NRHS / NR;
@@ -431,7 +394,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, int tile, in
         // every rhs of the bundle converged: the iteration is a no-op
         bool any_prob = false;
 #pragma unroll
-        for (int k = 0; k < NRHS; ++k) any_prob = any_prob || (a.state->active[k] != 0);
+        for (int k = 0; k < NRHS; ++k) any_prob = any_prob || (state->active[k] != 0);
         if (!any_prob) return;
     }
     const int g = threadIdx.x % G;
@@ -446,12 +409,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, int tile, in
     for (int k = 0; k < NR; ++k) {
         act[k] = false;
         alpha[k] = T(0);
-        if constexpr (EPI == EPI_CG) {
-            act[k] = a.state->active[g * NR + k] != 0;
-            alpha[k] = act[k] ? (T)a.state->alpha[g * NR + k] : T(0);
-        } else if constexpr (EPI == EPI_RESID) {
-            act[k] = a.state->sel[g * NR + k] != 0;
-        }
+        if constexpr (EPI == EPI_RESID) act[k] = state->sel[g * NR + k] != 0;
         any_act = any_act || act[k];
     }
     const T m4 = (T)a.mass4;
@@ -485,6 +443,28 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, int tile, in
         else
             dslash_site<T, NRHS, NR, NK, CM>(a.lat, a.parity, i, g, a.links, a.in, acc, ns);
         pin_acc(acc);
+    }
+    if constexpr (EPI == EPI_CG) {
+        // alpha = rr / <p, A p>, with <p, A p> = 4m^2 |p|^2 + |D_oe p|^2
+        // (D_eo^dag = -D_oe), for rhs lane mod NP in every wave; a rhs whose
+        // <p, A p> is not positive and finite is masked here and reported
+        constexpr int NP = sum_stride(NRHS);
+        const int kl = (int)(threadIdx.x & 63) % NP;
+        const double den = a.mass4 * sum_rows<NRHS>(a.pp) + sum_rows<NRHS>(a.tt);
+        const bool on = kl < NRHS && state->active[kl] != 0;
+        const bool good = den > 0.0 && finite_d(den);
+        const bool frozen = state->frozen != 0;
+        const T al = on && good && !frozen ? (T)(state->rr[kl] / den) : T(0);
+        if (bid == 0 && threadIdx.x < NRHS && on && !good && !frozen) state->brk[kl] = 1;
+        const int live = on && (good || frozen);
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            alpha[k] = __shfl(al, g * NR + k, 64);
+            act[k] = __shfl(live, g * NR + k, 64) != 0;
+            any_act = any_act || act[k];
+        }
+    }
+    if (on_site) {
         if constexpr (EPI == EPI_NORM) {
 #pragma unroll
             for (int c = 0; c < 3; ++c)
@@ -529,7 +509,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, int tile, in
     }
 
     bool last = false;
-    if constexpr (EPI != EPI_PLAIN) last = grid_reduce_post<NRHS, NR>(part, a.red, a.cnt, nblk, bid);
+    if constexpr (EPI != EPI_PLAIN) last = sum_post<NRHS, NR>(part, a.sum, nblk, bid);
 
     if (on_site) {
         if constexpr (EPI == EPI_PLAIN || EPI == EPI_NORM) {
@@ -555,10 +535,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, int tile, in
     }
 
     if constexpr (EPI != EPI_PLAIN) {
-        double total;
-        if (last && grid_reduce_finish<NRHS>(a.red, a.cnt, nblk, bid, &total)) {
-            if (threadIdx.x < NRHS) finish<EPI>(a.state, threadIdx.x, total, a.mass4);
-        }
+        if (last) sum_finish<NRHS>(a.sum, nblk, bid);
     }
 }
 
@@ -573,7 +550,7 @@ __global__ __launch_bounds__(kMaxBlock) HISQ_KATTR void k_dslash(const DslashArg
 {
     const int tile_sites = (int)blockDim.x / (NRHS / NR);
     dslash_tile<T, NRHS, NR, NK, EPI, CM>(
-        a, tile_of_block(blockIdx.x, gridDim.x, a.remap, a.lat, tile_sites), gridDim.x, blockIdx.x);
+        a, a.state, tile_of_block(blockIdx.x, gridDim.x, a.remap, a.lat, tile_sites), gridDim.x, blockIdx.x);
 }
 
 template <typename T, int NRHS, int NR, int NK, int EPI>
@@ -582,7 +559,7 @@ __global__ __launch_bounds__(kMaxBlockLds) void k_dslash_lds(const DslashArgs<T>
     extern __shared__ __align__(16) unsigned char hisq_stage[];
     const int tile_sites = (int)blockDim.x / (NRHS / NR);
     dslash_tile<T, NRHS, NR, NK, EPI, true, true>(
-        a, tile_of_block(blockIdx.x, gridDim.x, a.remap, a.lat, tile_sites), gridDim.x, blockIdx.x,
+        a, a.state, tile_of_block(blockIdx.x, gridDim.x, a.remap, a.lat, tile_sites), gridDim.x, blockIdx.x,
         reinterpret_cast<cplx<T>*>(hisq_stage));
 }
 
@@ -590,7 +567,7 @@ __global__ __launch_bounds__(kMaxBlockLds) void k_dslash_lds(const DslashArgs<T>
 // each work-group finds its problem (uniform scalar search over <= 16 entries)
 // and runs the body specialised for that problem's bundle size and tile.
 template <typename T, int NK, int EPI>
-__global__ __launch_bounds__(kMaxBlock) void k_dslash_batched(const BatchTable<T>* __restrict__ tab)
+__global__ __launch_bounds__(kMaxBlock) void k_dslash_batched(const BatchTable<T>* __restrict__ tab, int phase)
 {
     int q = 0;
     for (int j = 1; j < tab->nprob; ++j)
@@ -600,22 +577,23 @@ __global__ __launch_bounds__(kMaxBlock) void k_dslash_batched(const BatchTable<T
     if (bid >= bp.nblocks) return;
     const DslashArgs<T>& a = EPI == EPI_NORM ? bp.k2 : bp.k3;
     const int nb = bp.nblocks;
+    CgState* st = bp.state[state_of_phase(phase, 1)];
     // the problem's tile order, on its own block range (the blocks with equal
     // bid mod 8 still share one XCD)
     const int tile = tile_of_block(bid, nb, a.remap, a.lat, (int)blockDim.x / (bp.n / bp.nr));
     switch (bp.n * 16 + bp.nr) {
-    case 1 * 16 + 1: dslash_tile<T, 1, 1, NK, EPI, true>(a, tile, nb, bid); break;
-    case 2 * 16 + 2: dslash_tile<T, 2, 2, NK, EPI, true>(a, tile, nb, bid); break;
-    case 2 * 16 + 1: dslash_tile<T, 2, 1, NK, EPI, true>(a, tile, nb, bid); break;
-    case 3 * 16 + 3: dslash_tile<T, 3, 3, NK, EPI, true>(a, tile, nb, bid); break;
-    case 4 * 16 + 4: dslash_tile<T, 4, 4, NK, EPI, true>(a, tile, nb, bid); break;
-    case 4 * 16 + 2: dslash_tile<T, 4, 2, NK, EPI, true>(a, tile, nb, bid); break;
-    case 5 * 16 + 5: dslash_tile<T, 5, 5, NK, EPI, true>(a, tile, nb, bid); break;
-    case 6 * 16 + 6: dslash_tile<T, 6, 6, NK, EPI, true>(a, tile, nb, bid); break;
-    case 6 * 16 + 3: dslash_tile<T, 6, 3, NK, EPI, true>(a, tile, nb, bid); break;
-    case 7 * 16 + 7: dslash_tile<T, 7, 7, NK, EPI, true>(a, tile, nb, bid); break;
-    case 8 * 16 + 8: dslash_tile<T, 8, 8, NK, EPI, true>(a, tile, nb, bid); break;
-    case 8 * 16 + 4: dslash_tile<T, 8, 4, NK, EPI, true>(a, tile, nb, bid); break;
+    case 1 * 16 + 1: dslash_tile<T, 1, 1, NK, EPI, true>(a, st, tile, nb, bid); break;
+    case 2 * 16 + 2: dslash_tile<T, 2, 2, NK, EPI, true>(a, st, tile, nb, bid); break;
+    case 2 * 16 + 1: dslash_tile<T, 2, 1, NK, EPI, true>(a, st, tile, nb, bid); break;
+    case 3 * 16 + 3: dslash_tile<T, 3, 3, NK, EPI, true>(a, st, tile, nb, bid); break;
+    case 4 * 16 + 4: dslash_tile<T, 4, 4, NK, EPI, true>(a, st, tile, nb, bid); break;
+    case 4 * 16 + 2: dslash_tile<T, 4, 2, NK, EPI, true>(a, st, tile, nb, bid); break;
+    case 5 * 16 + 5: dslash_tile<T, 5, 5, NK, EPI, true>(a, st, tile, nb, bid); break;
+    case 6 * 16 + 6: dslash_tile<T, 6, 6, NK, EPI, true>(a, st, tile, nb, bid); break;
+    case 6 * 16 + 3: dslash_tile<T, 6, 3, NK, EPI, true>(a, st, tile, nb, bid); break;
+    case 7 * 16 + 7: dslash_tile<T, 7, 7, NK, EPI, true>(a, st, tile, nb, bid); break;
+    case 8 * 16 + 8: dslash_tile<T, 8, 8, NK, EPI, true>(a, st, tile, nb, bid); break;
+    case 8 * 16 + 4: dslash_tile<T, 8, 4, NK, EPI, true>(a, st, tile, nb, bid); break;
     default: break;
     }
 }
@@ -689,12 +667,12 @@ hipError_t HISQ_LAUNCH_NAME(int nrhs, const Tile& t, const DslashArgs<KT>& a, hi
 
 #if HISQ_KEPI == 1 || HISQ_KEPI == 2
 #define HISQ_BNAME HISQ_CAT(HISQ_CAT(HISQ_CAT(launch_dslash_batched_p, HISQ_KPREC), _e), HISQ_KEPI)
-hipError_t HISQ_BNAME(const BatchTable<KT>* tab, int total_blocks, int bs, hipStream_t s)
+hipError_t HISQ_BNAME(const BatchTable<KT>* tab, int total_blocks, int bs, int phase, hipStream_t s)
 {
     // built for at most kMaxBlock threads, whole waves (the grid reductions)
     if (bs < 64 || bs > kMaxBlock || bs % 64 != 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_dslash_batched<KT, kNK, HISQ_KEPI>), dim3(total_blocks), dim3(bs), 0, s,
-                       tab);
+                       tab, phase);
     return hipGetLastError();
 }
 #endif

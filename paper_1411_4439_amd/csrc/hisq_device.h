@@ -39,8 +39,6 @@ __device__ inline int tile_of_block(int b, int nb, int order, const Lat& lat, in
 
 __device__ inline double shfl_xor_d(double v, int m) { return __shfl_xor(v, m, 64); }
 
-constexpr int kRedGroup = 64;  // work-groups per second-stage group
-
 // Coherent accesses for the cross-work-group reduction.  Plain stores stay in
 // the L2 of the XCD that wrote them; agent-scope atomic accesses are performed
 // at the device-coherent level, so a work-group on another XCD sees them.
@@ -83,39 +81,41 @@ __device__ __forceinline__ double wave_sum(double v)
 // Per-rhs FP64 sums over the whole grid, in a fixed order (bitwise
 // reproducible, no floating-point atomics).  Each thread contributes part[k]
 // to rhs g*NR + k, where g = lane mod G is its rhs group.
-//   stage 1: wave butterflies + LDS -> one partial per work-group and rhs;
-//   stage 2: the last work-group of each group of 64 (atomic counter) sums the
-//            group's partials;
-//   stage 3: the last group to finish sums the group sums.
-// Only wave 0 of a work-group takes part after stage 1.  Returns true in wave 0
-// of the one work-group that finished last; lane k < NRHS then holds the total
-// of rhs k in *total.  The grid is the nblk work-groups of one problem, this
-// one being number bid.  red: [nblk][NRHS] partials then [ngroups][NRHS] group
-// sums; cnt: [1 + ngroups] counters, zero on entry and re-armed on exit.
+//   stage 1 (sum_post): wave butterflies + LDS -> one partial per work-group
+//            and rhs.  Where the grid has no more work-groups than rows, the
+//            partial is the row and the kernel is done: no counter, no wait.
+//   stage 2 (sum_post, sum_finish): else the last work-group of each group of
+//            `group` (atomic counter) sums the group's partials into its row.
+//   stage 3 (sum_rows): the kernel that needs the sum adds the rows, in every
+//            wave.  The end of the producing kernel orders the rows before it.
+// A third stage inside the producer (the last group sums the group sums) cost
+// each reducing kernel 2-3 us of counter and load round trips at its end, and
+// counters in one cache line another 10 ns per work-group: together 5 us of a
+// 16^3 x 4 to 32^3 x 8 kernel that streams for 5-25 us.
 //
-// Ordering.  A writer stores its partials with agent-scope atomic stores,
-// waits (s_waitcnt vmcnt(0)) until the memory system has acknowledged them --
-// an agent-scope atomic store is acknowledged once it is visible at the
-// device-coherent level, bypassing the XCD's non-coherent L2 -- and only then
-// issues its counter increment.  The last arriving work-group observes the
-// final count through the returned value of its own read-modify-write, then
-// executes an agent-scope acquire before it loads the partials with
-// agent-scope atomic loads.  So every partial was performed at the coherent
-// level before the increment that counted it, and every load of the reader
-// follows its observation of that count.  The writer side uses no release
-// fence: on this chip an agent-scope release writes back the XCD's whole L2,
-// which one work-group per launch can afford but every work-group cannot; the
-// completion wait orders exactly the stores the reader needs.
-// Stage 1 of grid_reduce_rhs: the work-group's partials are posted and its
-// group's counter advanced.  Returns true in wave 0 of the work-group that
-// arrived last in its group of 64, which must then call grid_reduce_finish.
-// A kernel may issue stores that the reduction does not read (its output
-// fields) between the two calls, so that the completion wait before the
-// counter update covers only the partials.
+// Ordering within a group.  A writer stores its partials with agent-scope
+// atomic stores, waits (s_waitcnt vmcnt(0)) until the memory system has
+// acknowledged them -- an agent-scope atomic store is acknowledged once it is
+// visible at the device-coherent level, bypassing the XCD's non-coherent L2 --
+// and only then issues its counter increment.  The last arriving work-group
+// observes the final count through the returned value of its own
+// read-modify-write, then executes an agent-scope acquire before it loads the
+// partials with agent-scope atomic loads.  So every partial was performed at
+// the coherent level before the increment that counted it, and every load of
+// the reader follows its observation of that count.  The writer side uses no
+// release fence: on this chip an agent-scope release writes back the XCD's
+// whole L2, which one work-group per launch can afford but every work-group
+// cannot; the completion wait orders exactly the stores the reader needs.
+//
+// sum_post returns true in wave 0 of the work-group that arrived last in its
+// group, which must then call sum_finish.  A kernel may issue stores that the
+// reduction does not read (its output fields) between the two calls, so that
+// the completion wait before the counter update covers only the partials.
 template <int NRHS, int NR>
-__device__ bool grid_reduce_post(double (&part)[NR], double* red, uint32_t* cnt, int nblk, int bid)
+__device__ bool sum_post(double (&part)[NR], const SumOut& o, int nblk, int bid)
 {
     constexpr int G = NRHS / NR;
+    constexpr int NP = sum_stride(NRHS);
     static_assert(G == 1 || G == 2 || G == 4 || G == 8, "rhs groups must be a power of two");
     __shared__ double sred[kMaxBlockLds / 64][kMaxRhs];
     const int lane = threadIdx.x & 63;
@@ -132,84 +132,125 @@ __device__ bool grid_reduce_post(double (&part)[NR], double* red, uint32_t* cnt,
     }
     __syncthreads();
     if (wave != 0) return false;
-    if (lane < NRHS) {
-        double s = 0;
+    double s = 0;
+    if (lane < NRHS)
         for (int w = 0; w < nwaves; ++w) s += sred[w][lane];
-        store_coherent(&red[(size_t)bid * NRHS + lane], s);
+    if (o.group == 1) {
+        if (lane < NP) o.rows[(size_t)bid * NP + lane] = s;
+        return false;
     }
+    if (lane < NP) store_coherent(&o.part[(size_t)bid * NP + lane], s);
     wait_memory();
-    const int grp = bid / kRedGroup;
-    const int gn = min(kRedGroup, nblk - grp * kRedGroup);
+    const int grp = bid / o.group;
+    const int gn = min(o.group, nblk - grp * o.group);
     uint32_t prev = 0;
-    if (lane == 0) prev = add_coherent(&cnt[1 + grp], 1u);
+    if (lane == 0) prev = add_coherent(&o.cnt[counter_index(grp)], 1u);
     prev = __shfl(prev, 0, 64);
     return prev == (uint32_t)(gn - 1);
 }
 
-// Stages 2 and 3, in wave 0 of a work-group for which grid_reduce_post
-// returned true: returns true in the one work-group that finished the grid,
-// where lane k < NRHS then holds the total of rhs k in *total.
+// Stage 2, in wave 0 of a work-group for which sum_post returned true.
 template <int NRHS>
-__device__ bool grid_reduce_finish(double* red, uint32_t* cnt, int nblk, int bid, double* total)
+__device__ void sum_finish(const SumOut& o, int nblk, int bid)
 {
+    constexpr int NP = sum_stride(NRHS);
+    constexpr int RL = 64 / NP;  // rows per pass: lane = (row, rhs)
     const int lane = threadIdx.x & 63;
-    const int ngroups = (nblk + kRedGroup - 1) / kRedGroup;
-    double* gsum = red + (size_t)nblk * NRHS;
-    const int grp = bid / kRedGroup;
-    const int g0 = grp * kRedGroup;
-    const int gn = min(kRedGroup, nblk - g0);
+    const int grp = bid / o.group;
+    const int g0 = grp * o.group;
+    const int gn = min(o.group, nblk - g0);
     acquire_agent();
-
-    // stage 2: the last work-group of the group
-    double acc[NRHS];
-    const double* row = &red[(size_t)(g0 + (lane < gn ? lane : 0)) * NRHS];
+    double v = 0;
+    for (int r0 = lane / NP; r0 < gn; r0 += 8 * RL) {
+        double x[8];
 #pragma unroll
-    for (int k = 0; k < NRHS; ++k) acc[k] = load_coherent(row + k);  // all loads in flight
-    double mine = 0;
+        for (int j = 0; j < 8; ++j) {  // all loads in flight
+            const int r = r0 + j * RL;
+            x[j] = r < gn ? load_coherent(&o.part[(size_t)(g0 + r) * NP + lane % NP]) : 0.0;
+        }
 #pragma unroll
-    for (int k = 0; k < NRHS; ++k) {
-        acc[k] = wave_sum(lane < gn ? acc[k] : 0.0);
-        if (lane == k) mine = acc[k];
+        for (int j = 0; j < 8; ++j) v += x[j];
     }
-    if (lane < NRHS) store_coherent(&gsum[(size_t)grp * NRHS + lane], mine);
-    if (lane == 0) store_coherent(&cnt[1 + grp], 0u);
-    wait_memory();
-    uint32_t prev = 0;
-    if (lane == 0) prev = add_coherent(&cnt[0], 1u);
-    prev = __shfl(prev, 0, 64);
-    if (prev != (uint32_t)(ngroups - 1)) return false;
-    acquire_agent();
-
-    // stage 3: the last group
 #pragma unroll
-    for (int k = 0; k < NRHS; ++k) acc[k] = 0.0;
-    for (int j = lane; j < ngroups; j += 64) {
-        double v[NRHS];
-#pragma unroll
-        for (int k = 0; k < NRHS; ++k) v[k] = load_coherent(&gsum[(size_t)j * NRHS + k]);
-#pragma unroll
-        for (int k = 0; k < NRHS; ++k) acc[k] += v[k];
-    }
-    mine = 0;
-#pragma unroll
-    for (int k = 0; k < NRHS; ++k) {
-        acc[k] = wave_sum(acc[k]);
-        if (lane == k) mine = acc[k];
-    }
-    if (lane == 0) store_coherent(&cnt[0], 0u);
-    *total = mine;
-    return true;
+    for (int off = 32; off >= NP; off >>= 1) v += shfl_xor_d(v, off);
+    if (lane < NP) o.rows[(size_t)grp * NP + lane] = v;
+    if (lane == 0) store_coherent(&o.cnt[counter_index(grp)], 0u);
 }
 
-template <int NRHS, int NR>
-__device__ bool grid_reduce_rhs(double (&part)[NR], double* red, uint32_t* cnt, int nblk, int bid,
-                                double* total)
+// Stage 3, in any wave with all lanes active: the total of rhs (lane mod
+// sum_stride(NRHS)), the same bits in every wave.
+template <int NRHS>
+__device__ __forceinline__ double sum_rows(const SumIn& in)
 {
-    if (!grid_reduce_post<NRHS, NR>(part, red, cnt, nblk, bid)) return false;
-    return grid_reduce_finish<NRHS>(red, cnt, nblk, bid, total);
+    constexpr int NP = sum_stride(NRHS);
+    constexpr int RL = 64 / NP;
+    const int lane = threadIdx.x & 63;
+    double x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int r = lane / NP + j * RL;
+        x[j] = r < in.n ? in.rows[(size_t)r * NP + lane % NP] : 0.0;
+    }
+    double v = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v += x[j];
+#pragma unroll
+    for (int off = 32; off >= NP; off >>= 1) v += shfl_xor_d(v, off);
+    return v;
 }
 
 __device__ inline bool finite_d(double v) { return v - v == 0.0; }
+
+// The scalars of rhs k = lane mod sum_stride(NRHS) at the start of an iteration:
+// those of src, advanced by the |r|^2 that the previous iteration left (unless
+// fresh: a poll block starts from what the host decided).  The wave that is the
+// launch's writer stores them to dst.  Every lane must be active.
+template <int NRHS>
+__device__ __forceinline__ void cg_scalars(const CgState* src, CgState* dst, const SumIn& rows, int fresh,
+                                           bool writer, bool& act, double& beta)
+{
+    constexpr int NP = sum_stride(NRHS);
+    const int lane = threadIdx.x & 63, k = lane % NP;
+    act = src->active[k] != 0;
+    beta = src->beta[k];
+    double rr = src->rr[k], rrmax = src->rrmax[k];
+    int iters = src->iters[k], status = src->status[k];
+    const double thresh = src->thresh[k];
+    if (!fresh) {
+        const double tot = sum_rows<NRHS>(rows);
+        if (act) {
+            if (src->brk[k]) {  // <p, A p> failed: x and r were not updated
+                status = HISQ_BREAKDOWN;
+                act = false;
+            } else {
+                iters += 1;
+                if (!finite_d(tot)) {
+                    status = HISQ_BREAKDOWN;
+                    act = false;
+                } else {
+                    beta = tot / rr;
+                    rr = tot;
+                    if (tot > rrmax) rrmax = tot;
+                    if (tot <= thresh || iters >= src->maxiter) act = false;
+                }
+            }
+        }
+    }
+    if (writer && lane < NP) {
+        dst->rr[k] = rr;
+        dst->beta[k] = beta;
+        dst->thresh[k] = thresh;
+        dst->rrmax[k] = rrmax;
+        dst->active[k] = act;
+        dst->status[k] = status;
+        dst->iters[k] = iters;
+        dst->brk[k] = 0;
+        if (lane == 0) {
+            dst->maxiter = src->maxiter;
+            dst->frozen = 0;
+        }
+    }
+}
 
 // Spinor field layouts, element (site i, colour c, rhs k) of an n-rhs field:
 //   site-major   [Vh][3][n]  (CM = false, the canonical layout at the boundary)

@@ -127,12 +127,54 @@ __host__ __device__ inline size_t slot_real_offset32(int r, int nr, int Vh, int 
     return (size_t)4 * nw * Vh + (size_t)i * rem + (r - 4 * nw);
 }
 
-// Per-problem CG scalars, in device memory (FP64).
+// Per-rhs sums over a grid.  The kernel that produces a sum leaves at most
+// kSumDoubles / np rows of partial sums (np: the bundle size rounded up to a
+// power of two, the row's stride), and every wave of the kernel that needs the
+// sum adds the rows itself: 8 loads per lane, no wait for a last work-group.
+// A grid of more work-groups than rows first sums groups of `sum_group`
+// consecutive work-groups into one row each.
+constexpr int kSumDoubles = 512;
+// Group counters are dealt over 64 cache lines of 128 bytes: atomics on one
+// line are served one after another (about 10 ns each), on different lines in
+// parallel.
+constexpr int kCounterLines = 64, kCounterStride = 32;
+__host__ __device__ constexpr int counter_index(int grp)
+{
+    return grp % kCounterLines * kCounterStride + grp / kCounterLines;
+}
+__host__ __device__ constexpr int sum_stride(int n) { return n <= 1 ? 1 : n <= 2 ? 2 : n <= 4 ? 4 : 8; }
+inline int sum_group(int nblk, int n)
+{
+    const int most = kSumDoubles / sum_stride(n);
+    return (nblk + most - 1) / most;
+}
+inline int sum_row_count(int nblk, int n)
+{
+    const int g = sum_group(nblk, n);
+    return (nblk + g - 1) / g;
+}
+
+// Where a reducing kernel leaves its sum.
+struct SumOut {
+    double* rows;   // [sum_row_count][sum_stride], read by the consumer
+    double* part;   // per-work-group partials (groups of more than one)
+    uint32_t* cnt;  // group counters (zero between launches)
+    int group;      // work-groups per row
+};
+
+// A finished sum as its consumer sees it.
+struct SumIn {
+    const double* rows;
+    int n;
+};
+
+// Per-problem CG scalars, in device memory (FP64).  The host reads and writes
+// one copy; inside a poll block the scalars pass through two further copies:
+// the p-update that starts an iteration reads the previous copy and the |r|^2
+// rows, and writes the next one, which the iteration's Dslash kernels read (so
+// no work-group reads a scalar that another one is writing).
 struct CgState {
     double rr[kMaxRhs];      // current (iterated) |r|^2
-    double pp[kMaxRhs];      // |p|^2 of this iteration
-    double tt[kMaxRhs];      // |D_oe p|^2 of this iteration
-    double alpha[kMaxRhs];
     double beta[kMaxRhs];
     double thresh[kMaxRhs];  // device-side masking threshold on rr
     double rr_true[kMaxRhs]; // |b - A x|^2 of the last true-residual pass
@@ -142,16 +184,17 @@ struct CgState {
     int32_t status[kMaxRhs];
     int32_t iters[kMaxRhs];
     int32_t sel[kMaxRhs];    // rhs selected for the next true-residual pass
+    int32_t brk[kMaxRhs];    // <p, A p> of this iteration was not positive and finite
     int32_t maxiter;
-    int32_t frozen;          // 1 while the autotuner times kernels: finishers write nothing
+    int32_t frozen;          // 1 while the autotuner times kernels: alpha = 0, nothing is recorded
     int32_t pad[6];
 };
 
 enum Epi {
     EPI_PLAIN = 0,  // out = D in
-    EPI_NORM = 1,   // t = D_oe p; |t|^2 -> tt, alpha
-    EPI_CG = 2,     // u = D_eo t; q = 4m^2 p - u; x += alpha p; r -= alpha q; |r|^2 -> rr, beta
-    EPI_RESID = 3   // (FP64) r = b - (4m^2 x - D_eo t) for selected rhs; |r|^2 -> rr_true
+    EPI_NORM = 1,   // t = D_oe p; |t|^2
+    EPI_CG = 2,     // alpha from |p|^2, |t|^2; u = D_eo t; q = 4m^2 p - u; x += alpha p; r -= alpha q; |r|^2
+    EPI_RESID = 3   // (FP64) r = b - (4m^2 x - D_eo t) for selected rhs; |r|^2
 };
 
 // Arguments of one Dslash launch (one problem).
@@ -171,8 +214,8 @@ struct DslashArgs {
     const d2* xh;
     double mass4;  // 4 m^2
     CgState* state;
-    double* red;    // reduction scratch: partials + group sums
-    uint32_t* cnt;  // reduction counters (zero between launches)
+    SumOut sum;   // where |t|^2, |r|^2 go
+    SumIn pp, tt;  // EPI_CG: |p|^2 and |t|^2 of this iteration
     int ntiles;
     int remap;
     int rows;  // LDS-staged x-rows per tile (0: unstaged)
@@ -184,20 +227,25 @@ struct PupdateArgs {
     Lat lat;
     const cplx<T>* r;
     cplx<T>* p;
-    CgState* state;
-    double* red;
-    uint32_t* cnt;
+    const CgState* src;  // scalars of the previous iteration, or the host's copy
+    CgState* dst;        // scalars of this iteration
+    SumIn rr;            // |r|^2 of the previous iteration (not with fresh)
+    int fresh;           // 1: beta and the masks stand in src as they are
+    SumOut sum;          // where |p|^2 goes
     int ntiles;
     int remap;
 };
 
 // One problem of a batched launch: the arguments of its three CG phases and
 // its range of work-groups in the flattened (problem, tile) grid.
+// k1.src / k1.dst / k2.state / k3.state are set from `state` by the launch's
+// phase (state_of_phase).
 template <typename T>
 struct BatchProb {
     PupdateArgs<T> k1;
     DslashArgs<T> k2;
     DslashArgs<T> k3;
+    CgState* state[3];  // the host's copy, then the two of the poll block
     int n;
     int nr;
     int block_start;
@@ -220,9 +268,20 @@ struct Tile {
     int rows = 0;  // > 0: LDS-staged Dslash, the work-group covers `rows` x-rows
 };
 
-// Reduction scratch for a grid of up to `blocks` work-groups.
-inline size_t red_doubles(size_t blocks) { return (blocks + (blocks + 63) / 64) * kMaxRhs; }
-inline size_t red_counters(size_t blocks) { return 1 + (blocks + 63) / 64; }
+// Iteration j of a poll block runs in phase 0 (j = 0), 1 (j odd) or 2 (j even):
+// it reads the copy state_of_phase(phase, 0) and writes state_of_phase(phase, 1).
+__host__ __device__ constexpr int state_of_phase(int phase, int dst)
+{
+    return dst ? (phase == 1 ? 2 : 1) : phase;
+}
+inline int phase_of(int j) { return j == 0 ? 0 : (j & 1) ? 1 : 2; }
+
+// Reduction scratch for a grid of up to `blocks` work-groups: the rows of the
+// three sums of an iteration (|p|^2, |t|^2, |r|^2), then the partials.
+enum SumSlot { SUM_PP = 0, SUM_TT = 1, SUM_RR = 2, SUM_SLOTS = 3 };
+inline size_t red_doubles(size_t blocks) { return (size_t)SUM_SLOTS * kSumDoubles + blocks * kMaxRhs; }
+constexpr size_t kRedCounters = (size_t)kCounterLines * kCounterStride;
+static_assert(kSumDoubles <= kCounterLines * kCounterStride, "a counter for every group");
 
 // Launchers, defined in the per-precision kernel objects.  cm selects the
 // colour-major field layout [3][Vh][n] (the solver's); the plain Dslash also
@@ -233,17 +292,29 @@ hipError_t launch_dslash_f64(int epi, int nrhs, const Tile& t, const DslashArgs<
 hipError_t launch_dslash_f32(int epi, int nk, int nrhs, const Tile& t, const DslashArgs<float>& a,
                              hipStream_t s, bool cm);
 hipError_t launch_dslash_batched_f64(int epi, const BatchTable<double>* tab, int total_blocks,
-                                     int bs, hipStream_t s);
+                                     int bs, int phase, hipStream_t s);
 hipError_t launch_dslash_batched_f32(int epi, int nk, const BatchTable<float>* tab,
-                                     int total_blocks, int bs, hipStream_t s);
+                                     int total_blocks, int bs, int phase, hipStream_t s);
 hipError_t launch_pupdate_batched_f64(const BatchTable<double>* tab, int total_blocks, int bs,
-                                      hipStream_t s);
+                                      int phase, hipStream_t s);
 hipError_t launch_pupdate_batched_f32(const BatchTable<float>* tab, int total_blocks, int bs,
-                                      hipStream_t s);
+                                      int phase, hipStream_t s);
+// End of a poll block: folds the last iteration (src, |r|^2 rows) into the
+// host's copy dst, for each of nprob problems.
+struct FoldArgs {
+    struct One {
+        const CgState* src;
+        CgState* dst;
+        SumIn rr;
+        int nrhs;
+    } p[HISQ_MAX_PROBLEMS];
+};
+hipError_t launch_fold(const FoldArgs& a, int nprob, hipStream_t s);
 // rhs-per-thread tiles the batched kernels are built for
 inline bool batched_nr_ok(int n, int nr) { return nr == n || (n % 2 == 0 && nr == n / 2); }
 // Streaming p-update for bundles of 1, 2, 4 or 8 rhs (any tile).
 inline bool pupdate_flat_ok(int n) { return n == 1 || n == 2 || n == 4 || n == 8; }
+int pupdate_flat_blocks(int nrhs, int Vh);
 hipError_t launch_pupdate_flat_f64(int nrhs, const PupdateArgs<double>& a, hipStream_t s);
 hipError_t launch_pupdate_flat_f32(int nrhs, const PupdateArgs<float>& a, hipStream_t s);
 hipError_t launch_pupdate_f64(int nrhs, const Tile& t, const PupdateArgs<double>& a,
@@ -254,9 +325,10 @@ hipError_t launch_pupdate_f32(int nrhs, const Tile& t, const PupdateArgs<float>&
 // Elementwise and reduction helpers (blas.hip).
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_state_reset(CgState* st, int nrhs, int active, hipStream_t s);
-// per-rhs |v|^2 of a colour-major FP64 field
-hipError_t launch_norm2_f64(const d2* v, int Vh, int nrhs, double* out, double* red,
-                            uint32_t* cnt, hipStream_t s);
+// out[k] = scale * (sum of rows, rhs k)
+hipError_t launch_sum_final(SumIn in, int nrhs, double scale, double* out, hipStream_t s);
+// per-rhs |v|^2 of a colour-major FP64 field; o: the reduction scratch (group is set here)
+hipError_t launch_norm2_f64(const d2* v, int Vh, int nrhs, double* out, SumOut o, hipStream_t s);
 hipError_t launch_to_f32_sel(const d2* src, f2* dst, size_t ncplx, int nrhs, const CgState* st,
                              hipStream_t s);
 hipError_t launch_accum_sel(d2* xh, f2* xl, size_t ncplx, int nrhs, const CgState* st,
@@ -274,7 +346,7 @@ hipError_t launch_dslash_dmu(const Lat& lat, int parity, int nrhs, int nder, con
                              const d2* in, d2* out, hipStream_t s);
 hipError_t launch_zero_sel(d2* v, size_t ncplx, int nrhs, const CgState* st, hipStream_t s);
 hipError_t launch_redot(const d2* y, const d2* x, int Vh, int nrhs, double scale, double* out,
-                        double* red, uint32_t* cnt, hipStream_t s);
+                        SumOut o, hipStream_t s);
 
 // The solve of hisq_cg_solve over a workspace region (api.cpp); host_buf, if
 // not NULL, holds HISQ_MAX_PROBLEMS host copies of the CG state in place of
