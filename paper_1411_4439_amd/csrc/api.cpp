@@ -320,37 +320,8 @@ hipError_t launch_ds(int epi, int n, int nk, const Tile& t, DslashArgs<float> a,
     return launch_dslash_f32(epi, nk, n, t, a, s, cm);
 }
 
-bool t_order_ok(const Lat& lat, int G, int bs, int order);
-
-// The tile of a kernel without LDS staging (the p-update, the batched
-// kernels): a staged Dslash tile may hold up to kMaxBlockLds threads, more
-// than those kernels are built for, so it falls back to 128 threads.
-Tile unstaged(const Tile& t)
-{
-    if (t.rows == 0 && t.bs <= kMaxBlock) return t;
-    return Tile{t.nr, 128, t.remap, 0};
-}
-
-int pup_blocks(const Lat& lat, int n, const Tile& t)
-{
-    return pupdate_flat_ok(n) ? pupdate_flat_blocks(n, lat.Vh) : tile_blocks(lat, n, unstaged(t));
-}
-
-hipError_t launch_pup(int n, const Tile& t, const PupdateArgs<double>& a, hipStream_t s)
-{
-    if (pupdate_flat_ok(n)) return launch_pupdate_flat_f64(n, a, s);
-    Tile u = unstaged(t);
-    if (!t_order_ok(a.lat, n / u.nr, u.bs, u.remap)) u.remap = 1;
-    return launch_pupdate_f64(n, u, a, s);
-}
-
-hipError_t launch_pup(int n, const Tile& t, const PupdateArgs<float>& a, hipStream_t s)
-{
-    if (pupdate_flat_ok(n)) return launch_pupdate_flat_f32(n, a, s);
-    Tile u = unstaged(t);
-    if (!t_order_ok(a.lat, n / u.nr, u.bs, u.remap)) u.remap = 1;
-    return launch_pupdate_f32(n, u, a, s);
-}
+hipError_t launch_pup(int n, const PupdateArgs<double>& a, hipStream_t s) { return launch_pupdate_f64(n, a, s); }
+hipError_t launch_pup(int n, const PupdateArgs<float>& a, hipStream_t s) { return launch_pupdate_f32(n, a, s); }
 
 // ---------------------------------------------------------------------------
 // Autotuner: times the candidate tiles with the plain Dslash on the caller's
@@ -432,8 +403,12 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
         ford = eo ? g_force_eo_order : g_force_order;
         frows = eo ? g_force_eo_rows : g_force_rows;
     }
+    // a reducing kernel's work-group covers at least least_sites(n) sites
+    auto enough = [&](int nr, int bs) { return epi == EPI_PLAIN || bs / (n / nr) >= least_sites(n); };
     if (mode == 1 && valid_nr(n, fnr)) {
-        const int sbs = cm ? staged_block(lat, n, n / fnr, frows, prec) : 0;
+        int sbs = cm ? staged_block(lat, n, n / fnr, frows, prec) : 0;
+        if (sbs && !enough(fnr, sbs)) sbs = 0;
+        while (!enough(fnr, fbs)) fbs *= 2;
         Tile t{fnr, sbs ? sbs : fbs, ford, sbs ? frows : 0};
         if (!t_order_ok(lat, n / fnr, t.bs, t.remap)) t.remap = 1;
         *out = t;
@@ -464,11 +439,12 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
     std::vector<Tile> cand;
     for (int G = 1; G <= 8; G *= 2) {
         if (n % G != 0) continue;
-        for (int bs : {64, 128, 256}) cand.push_back(Tile{n / G, bs, 0, 0});
+        for (int bs : {64, 128, 256})
+            if (enough(n / G, bs)) cand.push_back(Tile{n / G, bs, 0, 0});
         if (cm)
             for (int R = 1; R <= 16; ++R) {
                 const int sbs = staged_block(lat, n, G, R, prec);
-                if (sbs) cand.push_back(Tile{n / G, sbs, 0, R});
+                if (sbs && enough(n / G, sbs)) cand.push_back(Tile{n / G, sbs, 0, R});
             }
     }
     for (const Tile& base : cand) {
@@ -570,7 +546,7 @@ struct Engine {
     hipStream_t s = nullptr;
     CgState* states = nullptr;  // device, contiguous, one per problem
     void* table = nullptr;      // device BatchTable (several problems)
-    int batch_bs = 128, batch_blocks = 0;
+    int batch_bs = 128, batch_blocks = 0, batch_pup = 0;
     CgState* host_buf = nullptr;  // host copy of the states (NULL: the thread's pinned buffer)
     std::vector<hipEvent_t> ev;
     double kms[HISQ_K_COUNT] = {};
@@ -611,10 +587,10 @@ struct Engine {
     static CgState* state_copy(const Prob& q, int j) { return j == 0 ? q.w.st : q.w.cs + (j - 1); }
 
     // The arguments of the three kernels of an iteration in `phase` (phase_of),
-    // for grids of nb1, nb2 and nb3 work-groups.
+    // for Dslash grids of nb2 and nb3 work-groups.
     template <typename T>
     void iter_args(const Prob& q, PupdateArgs<T>& k1, DslashArgs<T>& k2, DslashArgs<T>& k3, int phase,
-                   int nb1, int nb2, int nb3) const
+                   int nb2, int nb3) const
     {
         const void* L = std::is_same<T, float>::value ? q.links32 : q.links64;
         const int rr = std::is_same<T, float>::value ? nk : HISQ_NAIK_FULL;
@@ -642,8 +618,6 @@ struct Engine {
         k1.dst = state_copy(q, state_of_phase(phase, 1));
         k1.rr = sum_in(q.w, SUM_RR, nb3, q.n);
         k1.fresh = phase == 0;
-        k1.sum = sum_out(q.w, SUM_PP, nb1, q.n);
-        k1.remap = tile.remap;
         k2 = DslashArgs<T>{};
         k2.lat = q.lat;
         k2.parity = 1;
@@ -653,11 +627,11 @@ struct Engine {
         k2.out = t;
         k2.mass4 = q.m4;
         k2.state = k1.dst;
-        k2.sum = sum_out(q.w, SUM_TT, nb2, q.n);
+        k2.sum = sum_out(q.w, SUM_PP, nb2, q.n);  // |p|^2, then |t|^2
         k2.remap = tile.remap;
         k3 = k2;
         k3.sum = sum_out(q.w, SUM_RR, nb3, q.n);
-        k3.pp = sum_in(q.w, SUM_PP, nb1, q.n);
+        k3.pp = sum_in(q.w, SUM_PP, nb2, q.n);
         k3.tt = sum_in(q.w, SUM_TT, nb2, q.n);
         k3.parity = 0;
         k3.links = link_block<T>(L, q.lat.Vh, rr, 0);
@@ -676,11 +650,11 @@ struct Engine {
         DslashArgs<T> k2, k3;
         const Tile& tile = std::is_same<T, float>::value ? q.t32 : q.t64;
         const Tile& tile_e = std::is_same<T, float>::value ? q.t32e : q.t64e;
-        iter_args<T>(q, k1, k2, k3, phase, pup_blocks(q.lat, q.n, tile), tile_blocks(q.lat, q.n, tile),
+        iter_args<T>(q, k1, k2, k3, phase, tile_blocks(q.lat, q.n, tile),
                      tile_blocks(q.lat, q.n, tile_e));
         const int rr = std::is_same<T, float>::value ? nk : HISQ_NAIK_FULL;
         if (evs) HIP_TRY(hipEventRecord(evs[0], st));
-        HIP_TRY(launch_pup(q.n, tile, k1, st));
+        HIP_TRY(launch_pup(q.n, k1, st));
         if (evs) HIP_TRY(hipEventRecord(evs[1], st));
         HIP_TRY(launch_ds(EPI_NORM, q.n, rr, tile, k2, st));
         if (evs) HIP_TRY(hipEventRecord(evs[2], st));
@@ -695,13 +669,13 @@ struct Engine {
         const BatchTable<T>* tab = reinterpret_cast<const BatchTable<T>*>(table);
         if (evs) HIP_TRY(hipEventRecord(evs[0], st));
         if constexpr (std::is_same<T, float>::value) {
-            HIP_TRY(launch_pupdate_batched_f32(tab, batch_blocks, batch_bs, phase, st));
+            HIP_TRY(launch_pupdate_batched_f32(tab, batch_pup, phase, st));
             if (evs) HIP_TRY(hipEventRecord(evs[1], st));
             HIP_TRY(launch_dslash_batched_f32(EPI_NORM, nk, tab, batch_blocks, batch_bs, phase, st));
             if (evs) HIP_TRY(hipEventRecord(evs[2], st));
             HIP_TRY(launch_dslash_batched_f32(EPI_CG, nk, tab, batch_blocks, batch_bs, phase, st));
         } else {
-            HIP_TRY(launch_pupdate_batched_f64(tab, batch_blocks, batch_bs, phase, st));
+            HIP_TRY(launch_pupdate_batched_f64(tab, batch_pup, phase, st));
             if (evs) HIP_TRY(hipEventRecord(evs[1], st));
             HIP_TRY(launch_dslash_batched_f64(EPI_NORM, tab, batch_blocks, batch_bs, phase, st));
             if (evs) HIP_TRY(hipEventRecord(evs[2], st));
@@ -746,7 +720,7 @@ struct Engine {
     {
         BatchTable<T>* tab = reinterpret_cast<BatchTable<T>*>(host_buf);
         std::memset(tab, 0, sizeof(*tab));
-        int start = 0;
+        int start = 0, pup = 0;
         const int np = which.empty() ? (int)P.size() : (int)which.size();
         for (int jj = 0; jj < np; ++jj) {
             const Prob& q = P[which.empty() ? jj : which[jj]];
@@ -754,20 +728,24 @@ struct Engine {
             bp.n = q.n;
             bp.nr = batch_nr(q);
             bp.nblocks = tile_blocks(q.lat, q.n, bp.nr, bs);
-            iter_args<T>(q, bp.k1, bp.k2, bp.k3, 0, bp.nblocks, bp.nblocks, bp.nblocks);
+            iter_args<T>(q, bp.k1, bp.k2, bp.k3, 0, bp.nblocks, bp.nblocks);
+            bp.pup_blocks = pupdate_blocks(q.n, q.lat.Vh, sizeof(T));
+            bp.pup_start = pup;
+            pup += bp.pup_blocks;
             // the tuner times the Dslash kernels on the host's (frozen) copy alone
             for (int c = 0; c < 3; ++c) bp.state[c] = state_copy(q, tuning ? 0 : c);
             // XCD-owned z-chunks where the problem's tiles allow, else one
             // contiguous slab per XCD
             const int G = q.n / bp.nr;
-            bp.k1.remap = bp.k2.remap = bp.k3.remap = t_order_ok(q.lat, G, bs, 3) ? 3 : 1;
-            bp.k1.ntiles = bp.k2.ntiles = bp.k3.ntiles = bp.nblocks;
+            bp.k2.remap = bp.k3.remap = t_order_ok(q.lat, G, bs, 3) ? 3 : 1;
+            bp.k2.ntiles = bp.k3.ntiles = bp.nblocks;
             bp.block_start = start;
             start += bp.nblocks;
         }
         tab->nprob = np;
         tab->total_blocks = start;
         batch_blocks = start;
+        batch_pup = pup;
         batch_bs = bs;
         HIP_TRY(hipMemcpyAsync(table, tab, sizeof(BatchTable<T>), hipMemcpyHostToDevice, s));
         HIP_TRY(hipStreamSynchronize(s));
@@ -1171,6 +1149,7 @@ int Engine::run(hisq_info* infos)
         DslashArgs<double> probe = args64(q, 1);
         probe.in = q.x;
         probe.out = q.w.t64;
+        probe.sum = sum_out(q.w, SUM_PP, 1, q.n);
         if ((rc = get_tile(q.lat, q.n, HISQ_PREC_F64, HISQ_NAIK_FULL, probe, s, &q.t64, EPI_NORM))) return rc;
         if (mixed && P.size() == 1) {
             DslashArgs<float> p32{};
@@ -1182,7 +1161,7 @@ int Engine::run(hisq_info* infos)
             p32.out = q.w.t32;
             p32.mass4 = q.m4;
             p32.state = q.w.st;
-            p32.sum = sum_out(q.w, SUM_TT, 1, q.n);
+            p32.sum = sum_out(q.w, SUM_PP, 1, q.n);
             if ((rc = get_tile(q.lat, q.n, HISQ_PREC_F32, nk, p32, s, &q.t32, EPI_NORM))) return rc;
         }
         // the D_eo kernel with the CG epilogue, timed on the iteration's own
@@ -1196,13 +1175,13 @@ int Engine::run(hisq_info* infos)
             if (mixed) {
                 PupdateArgs<float> k1;
                 DslashArgs<float> k2, k3;
-                iter_args<float>(q, k1, k2, k3, 0, 1, 1, 1);
+                iter_args<float>(q, k1, k2, k3, 0, 1, 1);
                 k3.state = q.w.st;
                 if ((rc = get_tile(q.lat, q.n, HISQ_PREC_F32, nk, k3, s, &q.t32e, EPI_CG))) return rc;
             } else {
                 PupdateArgs<double> k1;
                 DslashArgs<double> k2, k3;
-                iter_args<double>(q, k1, k2, k3, 0, 1, 1, 1);
+                iter_args<double>(q, k1, k2, k3, 0, 1, 1);
                 k3.state = q.w.st;
                 if ((rc = get_tile(q.lat, q.n, HISQ_PREC_F64, HISQ_NAIK_FULL, k3, s, &q.t64e, EPI_CG)))
                     return rc;

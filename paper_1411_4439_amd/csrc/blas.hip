@@ -1,267 +1,152 @@
-// CG vector kernels for gfx950: the masked p-update with its fused |p|^2,
+// CG vector kernels for gfx950: the masked p-update,
 // precision conversions for the reliable updates, and FP64 reductions.
 #include "hisq_device.h"
 
 namespace hisq {
 
-// The scalars that open an iteration, as this thread's rhs g*NR + k needs them;
-// false if no rhs of the bundle is active.
-template <int NRHS, int NR, typename T>
-__device__ __forceinline__ bool cg_begin(const CgState* src, CgState* dst, const SumIn& rr, int fresh,
-                                         bool writer, int g, bool (&act)[NR], T (&beta)[NR])
-{
-    bool on;
-    double b;
-    cg_scalars<NRHS>(src, dst, rr, fresh, writer, on, b);
-#pragma unroll
-    for (int k = 0; k < NR; ++k) {
-        act[k] = __shfl((int)on, g * NR + k, 64) != 0;
-        beta[k] = __shfl((T)b, g * NR + k, 64);
-    }
-    return __any(on);
-}
-
 // ---------------------------------------------------------------------------
-// p = r + beta_k p for every active rhs k; |p_k|^2 summed in FP64.
-// (site-tiled form, colour-major fields: bundles the streaming form does not cover)
-template <typename T, int NRHS, int NR>
-__device__ __forceinline__ void pupdate_tile(const PupdateArgs<T>& a, const CgState* src, CgState* dst,
-                                             int fresh, int tile, int nblk, int bid)
+// p = r + beta_k p for every active rhs k.  A stream of three field passes with
+// no reduction (|p|^2 is summed by D_oe, which reads p anyway): the field is
+// walked as a flat array of 16-byte chunks with a stride that is a multiple of
+// the rhs period, so every thread always touches the same rhs while each load
+// instruction covers a contiguous stretch of memory.  The first chunks are
+// requested before the scalars of the iteration are worked out.
+template <typename T, int NRHS>
+__device__ __forceinline__ void pupdate_flat(const PupdateArgs<T>& a, const CgState* src, CgState* dst,
+                                             int fresh, int nblk, int bid)
 {
     using C = cplx<T>;
-    constexpr int G = NRHS / NR;
-    const int g = threadIdx.x % G;
-    bool act[NR];
-    T beta[NR];
-    if (!cg_begin<NRHS, NR>(src, dst, a.rr, fresh, bid == 0 && threadIdx.x < 64, g, act, beta))
-        return;  // every rhs converged: nothing to do, nothing to reduce
-    bool any_act = false;
-    double part[NR];
+    constexpr int NV = 16 / sizeof(C);  // complex numbers per chunk
+    constexpr int U = 2;                // chunks in flight
+    const int nchunks = (int)((long)a.lat.Vh * 3 * NRHS / NV);
+    const int tid = bid * (int)blockDim.x + (int)threadIdx.x;
+    const int stride = nblk * (int)blockDim.x;  // times NV a multiple of NRHS
+    C rv[U][NV], pv[U][NV];
+    auto fetch = [&](int j) {
 #pragma unroll
-    for (int k = 0; k < NR; ++k) {
-        any_act = any_act || act[k];
-        part[k] = 0.0;
-    }
-    const int i = (tile * (int)blockDim.x + (int)threadIdx.x) / G;
-    const bool work = i < a.lat.Vh && any_act;
-    using Lay = Layout<NRHS, true>;
-    const int base = Lay::site(work ? i : 0) + g * NR;
-    C pv[3][NR];
-    if (work) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const int off = base + Lay::colour(c, a.lat.Vh);
-            C rv[NR];
-            load_rhs<NR>(a.r + off, rv);
-            load_rhs<NR>(a.p + off, pv[c]);
-#pragma unroll
-            for (int k = 0; k < NR; ++k) {
-                // beta = 0 starts (or restarts) the recursion: p = r exactly, even
-                // if p held non-finite values
-                pv[c][k] = beta[k] == T(0) ? rv[k]
-                                           : C{rv[k].x + beta[k] * pv[c][k].x, rv[k].y + beta[k] * pv[c][k].y};
-                if (act[k]) part[k] += (double)pv[c][k].x * pv[c][k].x + (double)pv[c][k].y * pv[c][k].y;
+        for (int u = 0; u < U; ++u)
+            if (j + u * stride < nchunks) {
+                load_rhs<NV>(a.r + (size_t)(j + u * stride) * NV, rv[u]);
+                load_rhs<NV>(a.p + (size_t)(j + u * stride) * NV, pv[u]);
             }
-        }
-    }
-    // partials first, then the stores (converged rhs are not written)
-    const bool last = sum_post<NRHS, NR>(part, a.sum, nblk, bid);
-    if (work) {
+    };
+    fetch(tid);
+    bool on;
+    double b;
+    cg_scalars<NRHS>(src, dst, a.rr, fresh, bid == 0 && threadIdx.x < 64, on, b);
+    if (!__any(on)) return;  // every rhs converged: nothing to do
+    bool act[NV], any_act = false;
+    T beta[NV];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) store_rhs_on<NR>(a.p + base + Lay::colour(c, a.lat.Vh), pv[c], act);
+    for (int v = 0; v < NV; ++v) {
+        const int k = (int)((long)tid * NV + v) % NRHS;
+        act[v] = __shfl((int)on, k, 64) != 0;
+        beta[v] = __shfl((T)b, k, 64);
+        any_act = any_act || act[v];
     }
-    if (last) sum_finish<NRHS>(a.sum, nblk, bid);
+    if (!any_act) return;
+    for (int j = tid; j < nchunks; j += U * stride) {
+        if (j != tid) fetch(j);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (j + u * stride < nchunks) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+                    // beta = 0 starts (or restarts) the recursion: p = r exactly,
+                    // even if p held non-finite values
+                    pv[u][v] = beta[v] == T(0) ? rv[u][v]
+                                               : C{rv[u][v].x + beta[v] * pv[u][v].x,
+                                                   rv[u][v].y + beta[v] * pv[u][v].y};
+                // converged rhs are not written
+                store_rhs_on<NV>(a.p + (size_t)(j + u * stride) * NV, pv[u], act);
+            }
+    }
 }
 
-template <typename T, int NRHS, int NR>
+template <typename T, int NRHS>
 __global__ __launch_bounds__(kMaxBlock) void k_pupdate(const PupdateArgs<T> a)
 {
-    pupdate_tile<T, NRHS, NR>(a, a.src, a.dst, a.fresh, tile_of_block(blockIdx.x, gridDim.x, a.remap, a.lat, (int)blockDim.x / (NRHS / NR)), gridDim.x,
-                              blockIdx.x);
+    pupdate_flat<T, NRHS>(a, a.src, a.dst, a.fresh, gridDim.x, blockIdx.x);
 }
 
+// One launch over the problems of a batch: each has its own range of work-groups.
 template <typename T>
 __global__ __launch_bounds__(kMaxBlock) void k_pupdate_batched(const BatchTable<T>* __restrict__ tab, int phase)
 {
     int q = 0;
     for (int j = 1; j < tab->nprob; ++j)
-        if ((int)blockIdx.x >= tab->p[j].block_start) q = j;
+        if ((int)blockIdx.x >= tab->p[j].pup_start) q = j;
     const BatchProb<T>& bp = tab->p[q];
-    const int bid = (int)blockIdx.x - bp.block_start;
-    if (bid >= bp.nblocks) return;
-    const int nb = bp.nblocks;
-    const int tile = tile_of_block(bid, nb, bp.k1.remap, bp.k1.lat, (int)blockDim.x / (bp.n / bp.nr));
+    const int bid = (int)blockIdx.x - bp.pup_start;
+    const int nb = bp.pup_blocks;
+    if (bid >= nb) return;
     const CgState* src = bp.state[state_of_phase(phase, 0)];
     CgState* dst = bp.state[state_of_phase(phase, 1)];
     const int fresh = phase == 0;
-    switch (bp.n * 16 + bp.nr) {
-    case 1 * 16 + 1: pupdate_tile<T, 1, 1>(bp.k1, src, dst, fresh, tile, nb, bid); break;
-    case 2 * 16 + 2: pupdate_tile<T, 2, 2>(bp.k1, src, dst, fresh, tile, nb, bid); break;
-    case 2 * 16 + 1: pupdate_tile<T, 2, 1>(bp.k1, src, dst, fresh, tile, nb, bid); break;
-    case 3 * 16 + 3: pupdate_tile<T, 3, 3>(bp.k1, src, dst, fresh, tile, nb, bid); break;
-    case 4 * 16 + 4: pupdate_tile<T, 4, 4>(bp.k1, src, dst, fresh, tile, nb, bid); break;
-    case 4 * 16 + 2: pupdate_tile<T, 4, 2>(bp.k1, src, dst, fresh, tile, nb, bid); break;
-    case 5 * 16 + 5: pupdate_tile<T, 5, 5>(bp.k1, src, dst, fresh, tile, nb, bid); break;
-    case 6 * 16 + 6: pupdate_tile<T, 6, 6>(bp.k1, src, dst, fresh, tile, nb, bid); break;
-    case 6 * 16 + 3: pupdate_tile<T, 6, 3>(bp.k1, src, dst, fresh, tile, nb, bid); break;
-    case 7 * 16 + 7: pupdate_tile<T, 7, 7>(bp.k1, src, dst, fresh, tile, nb, bid); break;
-    case 8 * 16 + 8: pupdate_tile<T, 8, 8>(bp.k1, src, dst, fresh, tile, nb, bid); break;
-    case 8 * 16 + 4: pupdate_tile<T, 8, 4>(bp.k1, src, dst, fresh, tile, nb, bid); break;
+    switch (bp.n) {
+    case 1: pupdate_flat<T, 1>(bp.k1, src, dst, fresh, nb, bid); break;
+    case 2: pupdate_flat<T, 2>(bp.k1, src, dst, fresh, nb, bid); break;
+    case 3: pupdate_flat<T, 3>(bp.k1, src, dst, fresh, nb, bid); break;
+    case 4: pupdate_flat<T, 4>(bp.k1, src, dst, fresh, nb, bid); break;
+    case 5: pupdate_flat<T, 5>(bp.k1, src, dst, fresh, nb, bid); break;
+    case 6: pupdate_flat<T, 6>(bp.k1, src, dst, fresh, nb, bid); break;
+    case 7: pupdate_flat<T, 7>(bp.k1, src, dst, fresh, nb, bid); break;
+    case 8: pupdate_flat<T, 8>(bp.k1, src, dst, fresh, nb, bid); break;
     default: break;
     }
 }
 
-// Streaming form of the p-update for bundles of 1, 2, 4 or 8 rhs: the field is
-// walked as a flat array of NRT-complex chunks with a stride that is a
-// multiple of the rhs period, so every thread always touches the same NRT rhs
-// (and the lanes of a wave with equal lane mod (NRHS/NRT) the same ones) while
-// each load instruction covers a contiguous stretch of memory.
-template <typename T, int NRHS, int NRT>
-__global__ __launch_bounds__(kMaxBlock) void k_pupdate_flat(const PupdateArgs<T> a, long nchunks)
+constexpr int kPupBlock = 256, kPupMaxBlocks = 2048;
+
+// Enough work-groups for one pass, at most 8 per CU, a multiple of the rhs period.
+int pupdate_blocks(int nrhs, int Vh, size_t elem)
 {
-    using C = cplx<T>;
-    constexpr int G = NRHS / NRT;
-    const long tid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long stride = (long)gridDim.x * blockDim.x;  // a multiple of 64, hence of G
-    const int g = (int)(tid % G);
-    bool act[NRT];
-    T beta[NRT];
-    if (!cg_begin<NRHS, NRT>(a.src, a.dst, a.rr, a.fresh, blockIdx.x == 0 && threadIdx.x < 64, g, act, beta))
-        return;
-    double part[NRT];
-    bool any_act = false;
-#pragma unroll
-    for (int k = 0; k < NRT; ++k) {
-        any_act = any_act || act[k];
-        part[k] = 0.0;
-    }
-    if (any_act) {
-        for (long j = tid; j < nchunks; j += stride) {
-            C rv[NRT], pv[NRT];
-            load_rhs<NRT>(a.r + j * NRT, rv);
-            load_rhs<NRT>(a.p + j * NRT, pv);
-#pragma unroll
-            for (int k = 0; k < NRT; ++k) {
-                pv[k] = beta[k] == T(0) ? rv[k]
-                                        : C{rv[k].x + beta[k] * pv[k].x, rv[k].y + beta[k] * pv[k].y};
-                if (act[k]) part[k] += (double)pv[k].x * pv[k].x + (double)pv[k].y * pv[k].y;
-            }
-            store_rhs_on<NRT>(a.p + j * NRT, pv, act);
-        }
-    }
-    if (sum_post<NRHS, NRT>(part, a.sum, gridDim.x, blockIdx.x))
-        sum_finish<NRHS>(a.sum, gridDim.x, blockIdx.x);
-}
-
-constexpr int kFlatMaxBlocks = 2048;
-
-// complex numbers per thread and step
-static constexpr int flat_chunk(int nrhs) { return nrhs >= 2 ? 2 : 1; }
-
-int pupdate_flat_blocks(int nrhs, int Vh)
-{
-    const long nchunks = (long)Vh * 3 * nrhs / flat_chunk(nrhs);
-    const long blocks = (nchunks + 255) / 256;
-    return (int)(blocks > kFlatMaxBlocks ? kFlatMaxBlocks : blocks);
-}
-
-template <typename T, int NRHS>
-static hipError_t go_flat(PupdateArgs<T> a, hipStream_t s)
-{
-    constexpr int NRT = flat_chunk(NRHS);
-    const long nchunks = (long)a.lat.Vh * 3 * NRHS / NRT;
-    const int blocks = pupdate_flat_blocks(NRHS, a.lat.Vh);
-    hipLaunchKernelGGL((k_pupdate_flat<T, NRHS, NRT>), dim3(blocks), dim3(256), 0, s, a, nchunks);
-    return hipGetLastError();
+    const long nchunks = (long)Vh * 3 * nrhs * 2 * (long)elem / 16;
+    long blocks = (nchunks + kPupBlock - 1) / kPupBlock;
+    if (blocks > kPupMaxBlocks) blocks = kPupMaxBlocks;
+    return (int)((blocks + nrhs - 1) / nrhs * nrhs);
 }
 
 template <typename T>
-static hipError_t launch_flat(int nrhs, const PupdateArgs<T>& a, hipStream_t s)
+static hipError_t launch_pupdate(int nrhs, const PupdateArgs<T>& a, hipStream_t s)
 {
+    const dim3 grid(pupdate_blocks(nrhs, a.lat.Vh, sizeof(T))), block(kPupBlock);
     switch (nrhs) {
-    case 1: return go_flat<T, 1>(a, s);
-    case 2: return go_flat<T, 2>(a, s);
-    case 4: return go_flat<T, 4>(a, s);
-    case 8: return go_flat<T, 8>(a, s);
+    case 1: hipLaunchKernelGGL((k_pupdate<T, 1>), grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((k_pupdate<T, 2>), grid, block, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((k_pupdate<T, 3>), grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((k_pupdate<T, 4>), grid, block, 0, s, a); break;
+    case 5: hipLaunchKernelGGL((k_pupdate<T, 5>), grid, block, 0, s, a); break;
+    case 6: hipLaunchKernelGGL((k_pupdate<T, 6>), grid, block, 0, s, a); break;
+    case 7: hipLaunchKernelGGL((k_pupdate<T, 7>), grid, block, 0, s, a); break;
+    case 8: hipLaunchKernelGGL((k_pupdate<T, 8>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
     }
-}
-
-hipError_t launch_pupdate_flat_f64(int nrhs, const PupdateArgs<double>& a, hipStream_t s)
-{
-    return launch_flat<double>(nrhs, a, s);
-}
-
-hipError_t launch_pupdate_flat_f32(int nrhs, const PupdateArgs<float>& a, hipStream_t s)
-{
-    return launch_flat<float>(nrhs, a, s);
-}
-
-hipError_t launch_pupdate_batched_f64(const BatchTable<double>* tab, int total_blocks, int bs,
-                                      int phase, hipStream_t s)
-{
-    if (bs < 64 || bs > kMaxBlock || bs % 64 != 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pupdate_batched<double>, dim3(total_blocks), dim3(bs), 0, s, tab, phase);
     return hipGetLastError();
 }
 
-hipError_t launch_pupdate_batched_f32(const BatchTable<float>* tab, int total_blocks, int bs,
-                                      int phase, hipStream_t s)
+hipError_t launch_pupdate_f64(int nrhs, const PupdateArgs<double>& a, hipStream_t s)
 {
-    if (bs < 64 || bs > kMaxBlock || bs % 64 != 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pupdate_batched<float>, dim3(total_blocks), dim3(bs), 0, s, tab, phase);
+    return launch_pupdate<double>(nrhs, a, s);
+}
+
+hipError_t launch_pupdate_f32(int nrhs, const PupdateArgs<float>& a, hipStream_t s)
+{
+    return launch_pupdate<float>(nrhs, a, s);
+}
+
+hipError_t launch_pupdate_batched_f64(const BatchTable<double>* tab, int total_blocks, int phase,
+                                      hipStream_t s)
+{
+    hipLaunchKernelGGL(k_pupdate_batched<double>, dim3(total_blocks), dim3(kPupBlock), 0, s, tab, phase);
     return hipGetLastError();
 }
 
-template <typename T, int NRHS, int NR>
-static hipError_t go_pup(const Tile& t, PupdateArgs<T> a, hipStream_t s)
+hipError_t launch_pupdate_batched_f32(const BatchTable<float>* tab, int total_blocks, int phase,
+                                      hipStream_t s)
 {
-    constexpr int G = NRHS / NR;
-    if (t.bs < 64 || t.bs > kMaxBlock || t.bs % 64 != 0) return hipErrorInvalidValue;
-    const long threads = (long)a.lat.Vh * G;
-    a.ntiles = (int)((threads + t.bs - 1) / t.bs);
-    a.remap = t.remap;
-    hipLaunchKernelGGL((k_pupdate<T, NRHS, NR>), dim3(a.ntiles), dim3(t.bs), 0, s, a);
+    hipLaunchKernelGGL(k_pupdate_batched<float>, dim3(total_blocks), dim3(kPupBlock), 0, s, tab, phase);
     return hipGetLastError();
-}
-
-template <typename T, int NRHS>
-static hipError_t pick_pup(const Tile& t, const PupdateArgs<T>& a, hipStream_t s)
-{
-    if (t.nr == NRHS) return go_pup<T, NRHS, NRHS>(t, a, s);
-    if constexpr (NRHS % 2 == 0)
-        if (t.nr == NRHS / 2) return go_pup<T, NRHS, NRHS / 2>(t, a, s);
-    if constexpr (NRHS % 4 == 0)
-        if (t.nr == NRHS / 4) return go_pup<T, NRHS, NRHS / 4>(t, a, s);
-    if constexpr (NRHS % 8 == 0)
-        if (t.nr == NRHS / 8) return go_pup<T, NRHS, NRHS / 8>(t, a, s);
-    return hipErrorInvalidValue;
-}
-
-template <typename T>
-static hipError_t launch_pupdate(int nrhs, const Tile& t, const PupdateArgs<T>& a, hipStream_t s)
-{
-    switch (nrhs) {
-    case 1: return pick_pup<T, 1>(t, a, s);
-    case 2: return pick_pup<T, 2>(t, a, s);
-    case 3: return pick_pup<T, 3>(t, a, s);
-    case 4: return pick_pup<T, 4>(t, a, s);
-    case 5: return pick_pup<T, 5>(t, a, s);
-    case 6: return pick_pup<T, 6>(t, a, s);
-    case 7: return pick_pup<T, 7>(t, a, s);
-    case 8: return pick_pup<T, 8>(t, a, s);
-    default: return hipErrorInvalidValue;
-    }
-}
-
-hipError_t launch_pupdate_f64(int nrhs, const Tile& t, const PupdateArgs<double>& a, hipStream_t s)
-{
-    return launch_pupdate<double>(nrhs, t, a, s);
-}
-
-hipError_t launch_pupdate_f32(int nrhs, const Tile& t, const PupdateArgs<float>& a, hipStream_t s)
-{
-    return launch_pupdate<float>(nrhs, t, a, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -462,9 +347,9 @@ hipError_t launch_layout(const d2* src, d2* dst, int Vh, int nrhs, bool to_colou
 template <int NRHS>
 __global__ __launch_bounds__(kMaxBlock) void k_norm2(const d2* __restrict__ v, int Vh, SumOut o)
 {
-    double part[NRHS];
+    double part[1][NRHS];
 #pragma unroll
-    for (int k = 0; k < NRHS; ++k) part[k] = 0.0;
+    for (int k = 0; k < NRHS; ++k) part[0][k] = 0.0;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < Vh) {
 #pragma unroll
@@ -472,11 +357,11 @@ __global__ __launch_bounds__(kMaxBlock) void k_norm2(const d2* __restrict__ v, i
 #pragma unroll
             for (int k = 0; k < NRHS; ++k) {
                 const d2 e = v[((size_t)c * Vh + i) * NRHS + k];
-                part[k] += e.x * e.x + e.y * e.y;
+                part[0][k] += e.x * e.x + e.y * e.y;
             }
     }
-    if (sum_post<NRHS, NRHS>(part, o, gridDim.x, blockIdx.x))
-        sum_finish<NRHS>(o, gridDim.x, blockIdx.x);
+    if (sum_post<NRHS, NRHS, 1>(part, o, gridDim.x, blockIdx.x))
+        sum_finish<NRHS, 1>(o, gridDim.x, blockIdx.x);
 }
 
 hipError_t launch_norm2_f64(const d2* v, int Vh, int nrhs, double* out, SumOut o, hipStream_t s)
@@ -509,16 +394,16 @@ __global__ __launch_bounds__(kMaxBlock) void k_redot(const d2* __restrict__ y,
                                                      const d2* __restrict__ x, int Vh, int nrhs,
                                                      SumOut o)
 {
-    double part[1] = {0.0};
+    double part[1][1] = {{0.0}};
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < Vh) {
         for (int e = 0; e < 3 * nrhs; ++e) {
             const d2 a = y[(size_t)i * 3 * nrhs + e];
             const d2 b = x[(size_t)i * 3 * nrhs + e];
-            part[0] += a.x * b.x + a.y * b.y;
+            part[0][0] += a.x * b.x + a.y * b.y;
         }
     }
-    if (sum_post<1, 1>(part, o, gridDim.x, blockIdx.x)) sum_finish<1>(o, gridDim.x, blockIdx.x);
+    if (sum_post<1, 1, 1>(part, o, gridDim.x, blockIdx.x)) sum_finish<1, 1>(o, gridDim.x, blockIdx.x);
 }
 
 hipError_t launch_redot(const d2* y, const d2* x, int Vh, int nrhs, double scale, double* out,

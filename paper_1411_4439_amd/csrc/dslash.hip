@@ -113,6 +113,20 @@ __host__ __device__ constexpr int slot_at(int k)
     return ((k & 1) ? ((k >> 3) & 1) : 2 + ((k >> 3) & 1)) + 4 * ((k >> 1) & 3);
 }
 
+template <typename T>
+__device__ __forceinline__ double norm2c(cplx<T> v)
+{
+    return (double)v.x * (double)v.x + (double)v.y * (double)v.y;
+}
+
+template <typename T, int NR>
+__device__ __forceinline__ void own_norm(const cplx<T> (&v)[3][NR], double (&own)[NR])
+{
+#pragma unroll
+    for (int k = 0; k < NR; ++k)
+        own[k] = norm2c<T>(v[0][k]) + norm2c<T>(v[1][k]) + norm2c<T>(v[2][k]);
+}
+
 // acc[c][k] = (D in)_{i}, colour c, rhs g*NR + k, output parity P.
 // Slot s = 4*hop + mu applies matrix s of the parity block to the neighbour
 // reached by hop (+1, -1, +3, -3) in direction mu.  The 16 slots run as a
@@ -121,11 +135,17 @@ __host__ __device__ constexpr int slot_at(int k)
 // the longest latency; neighbour vectors mostly hit L2).  The scheduling
 // barriers keep the compiler from hoisting further loads, which would
 // otherwise exhaust the register file.
-template <typename T, int NRHS, int NR, int NK, bool CM>
+//
+// With PN, own[k] = |in_i|^2, the field at the site's own index: the half-site
+// of the other parity one step away in x, a line that the +1 or -1 x-slot has
+// brought already.  It is read as a 17th slot without a link, into the buffer
+// that the last slot leaves free; summing it from the x-slot itself (which of
+// the two it is depends on x) broke the pipeline and spilled.
+template <typename T, int NRHS, int NR, int NK, bool CM, bool PN>
 __device__ __forceinline__ void dslash_site(const Lat& lat, int P, int i, int g,
                                             const cplx<T>* __restrict__ lk,
                                             const cplx<T>* __restrict__ in,
-                                            cplx<T> (&acc)[3][NR], T ns)
+                                            cplx<T> (&acc)[3][NR], T ns, double (&own)[NR])
 {
     using C = cplx<T>;
     const int Vh = lat.Vh;
@@ -155,12 +175,15 @@ __device__ __forceinline__ void dslash_site(const Lat& lat, int P, int i, int g,
             load_link_part<T, NK, slot_at(k + LD), G>(lk, Vh, i, gl, lr[(k + LD) % (LD + 1)]);
         if constexpr (k + 1 < 16)
             load_vec<T, NRHS, NR, CM>(in, Vh, neighbour<slot_at(k + 1)>(lat, sc), g, v[(k + 1) & 1]);
+        else if constexpr (PN)
+            load_vec<T, NRHS, NR, CM>(in, Vh, i, g, v[(k + 1) & 1]);
         __builtin_amdgcn_sched_barrier(0);
         C m[9];
         share_link<T, NK, slot_at(k), G>(lr[k % (LD + 1)], m);
         apply_slot<T, NR, NK, slot_at(k)>(m, v[k & 1], acc, ns);
         __builtin_amdgcn_sched_barrier(0);
     });
+    if constexpr (PN) own_norm<T, NR>(v[0], own);
 }
 
 // ---------------------------------------------------------------------------
@@ -309,13 +332,13 @@ __device__ __forceinline__ void lds_head(const Lat& lat, int P, int i, int g,
     load_vec<T, NRHS, NR, true>(in, lat.Vh, neighbour<slot_at(2)>(lat, sc), g, h.v1);
 }
 
-template <typename T, int NRHS, int NR, int NK>
+template <typename T, int NRHS, int NR, int NK, bool PN>
 __device__ __forceinline__ void dslash_site_lds(const Lat& lat, int P, int i, int g, int r,
                                                 const cplx<T>* __restrict__ lk,
                                                 const cplx<T>* __restrict__ in,
                                                 const cplx<T>* lds, int rows,
                                                 const LdsHead<T, NRHS, NR, NK>& h,
-                                                cplx<T> (&acc)[3][NR], T ns)
+                                                cplx<T> (&acc)[3][NR], T ns, double (&own)[NR])
 {
     using C = cplx<T>;
     const int Vh = lat.Vh;
@@ -361,6 +384,10 @@ __device__ __forceinline__ void dslash_site_lds(const Lat& lat, int P, int i, in
         }
         __builtin_amdgcn_sched_barrier(0);
     });
+    if constexpr (PN) {
+        load_vec_lds<T, NRHS, NR>(lds, cstride, (r + 3) * lat.Lh0 + xh, g, vl);
+        own_norm<T, NR>(vl, own);
+    }
 }
 
 // An empty asm that reads every accumulator: keeps the compiler from sinking
@@ -373,12 +400,6 @@ __device__ __forceinline__ void pin_acc(C (&acc)[3][NR])
     for (int c = 0; c < 3; ++c)
 #pragma unroll
         for (int k = 0; k < NR; ++k) asm volatile("" ::"v"(acc[c][k].x), "v"(acc[c][k].y));
-}
-
-template <typename T>
-__device__ __forceinline__ double norm2c(cplx<T> v)
-{
-    return (double)v.x * (double)v.x + (double)v.y * (double)v.y;
 }
 
 // One tile (one work-group's worth of sites) of a half-Dslash with epilogue
@@ -398,9 +419,12 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
         if (!any_prob) return;
     }
     const int g = threadIdx.x % G;
-    double part[NR];
+    constexpr int M = EPI == EPI_NORM ? 2 : 1;  // |p|^2 and |t|^2, or one sum
+    double part[M][NR];
 #pragma unroll
-    for (int k = 0; k < NR; ++k) part[k] = 0.0;
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int k = 0; k < NR; ++k) part[m][k] = 0.0;
 
     bool act[NR];
     T alpha[NR];
@@ -437,11 +461,12 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
     d2 rr[3][NR];            // EPI_RESID: the FP64 residual
     if (on_site) {
         if constexpr (ST)
-            dslash_site_lds<T, NRHS, NR, NK>(a.lat, a.parity, i, g,
-                                              ((int)threadIdx.x / G) / a.lat.Lh0, a.links, a.in,
-                                              lds, a.rows + 6, head, acc, ns);
+            dslash_site_lds<T, NRHS, NR, NK, EPI == EPI_NORM>(
+                a.lat, a.parity, i, g, ((int)threadIdx.x / G) / a.lat.Lh0, a.links, a.in, lds,
+                a.rows + 6, head, acc, ns, part[0]);
         else
-            dslash_site<T, NRHS, NR, NK, CM>(a.lat, a.parity, i, g, a.links, a.in, acc, ns);
+            dslash_site<T, NRHS, NR, NK, CM, EPI == EPI_NORM>(a.lat, a.parity, i, g, a.links, a.in,
+                                                              acc, ns, part[0]);
         pin_acc(acc);
     }
     if constexpr (EPI == EPI_CG) {
@@ -469,7 +494,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
 #pragma unroll
             for (int c = 0; c < 3; ++c)
 #pragma unroll
-                for (int k = 0; k < NR; ++k) part[k] += norm2c<T>(acc[c][k]);
+                for (int k = 0; k < NR; ++k) part[M - 1][k] += norm2c<T>(acc[c][k]);
         } else if constexpr (EPI == EPI_CG) {
             if (any_act) {
             // converged (masked) rhs are not written (and not read where the
@@ -486,7 +511,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
                     const C q = C{m4 * pv[k].x - acc[c][k].x, m4 * pv[k].y - acc[c][k].y};
                     xo[c][k] = C{xo[c][k].x + alpha[k] * pv[k].x, xo[c][k].y + alpha[k] * pv[k].y};
                     ro[c][k] = C{ro[c][k].x - alpha[k] * q.x, ro[c][k].y - alpha[k] * q.y};
-                    if (act[k]) part[k] += norm2c<T>(ro[c][k]);
+                    if (act[k]) part[0][k] += norm2c<T>(ro[c][k]);
                 }
             }
             }
@@ -501,7 +526,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
                 for (int k = 0; k < NR; ++k) {
                     rr[c][k] = d2{bv[k].x - (m4 * xv[k].x - acc[c][k].x),
                                   bv[k].y - (m4 * xv[k].y - acc[c][k].y)};
-                    part[k] += norm2c<double>(rr[c][k]);
+                    part[0][k] += norm2c<double>(rr[c][k]);
                 }
             }
             }
@@ -509,7 +534,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
     }
 
     bool last = false;
-    if constexpr (EPI != EPI_PLAIN) last = sum_post<NRHS, NR>(part, a.sum, nblk, bid);
+    if constexpr (EPI != EPI_PLAIN) last = sum_post<NRHS, NR, M>(part, a.sum, nblk, bid);
 
     if (on_site) {
         if constexpr (EPI == EPI_PLAIN || EPI == EPI_NORM) {
@@ -535,7 +560,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
     }
 
     if constexpr (EPI != EPI_PLAIN) {
-        if (last) sum_finish<NRHS>(a.sum, nblk, bid);
+        if (last) sum_finish<NRHS, M>(a.sum, nblk, bid);
     }
 }
 

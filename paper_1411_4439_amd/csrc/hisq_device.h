@@ -111,35 +111,41 @@ __device__ __forceinline__ double wave_sum(double v)
 // group, which must then call sum_finish.  A kernel may issue stores that the
 // reduction does not read (its output fields) between the two calls, so that
 // the completion wait before the counter update covers only the partials.
-template <int NRHS, int NR>
-__device__ bool sum_post(double (&part)[NR], const SumOut& o, int nblk, int bid)
+// M sums at once: part[m][k].
+template <int NRHS, int NR, int M>
+__device__ bool sum_post(double (&part)[M][NR], const SumOut& o, int nblk, int bid)
 {
     constexpr int G = NRHS / NR;
     constexpr int NP = sum_stride(NRHS);
     static_assert(G == 1 || G == 2 || G == 4 || G == 8, "rhs groups must be a power of two");
-    __shared__ double sred[kMaxBlockLds / 64][kMaxRhs];
+    __shared__ double sred[kMaxBlockLds / 64][M * kMaxRhs];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int nwaves = blockDim.x >> 6;
 #pragma unroll
-    for (int k = 0; k < NR; ++k) {
+    for (int m = 0; m < M; ++m)
 #pragma unroll
-        for (int off = 32; off >= G; off >>= 1) part[k] += shfl_xor_d(part[k], off);
-    }
+        for (int k = 0; k < NR; ++k) {
+#pragma unroll
+            for (int off = 32; off >= G; off >>= 1) part[m][k] += shfl_xor_d(part[m][k], off);
+        }
     if (lane < G) {
 #pragma unroll
-        for (int k = 0; k < NR; ++k) sred[wave][lane * NR + k] = part[k];
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int k = 0; k < NR; ++k) sred[wave][m * NP + lane * NR + k] = part[m][k];
     }
     __syncthreads();
     if (wave != 0) return false;
     double s = 0;
-    if (lane < NRHS)
+    const int k = lane % NP, m = lane / NP;
+    if (k < NRHS && m < M)
         for (int w = 0; w < nwaves; ++w) s += sred[w][lane];
     if (o.group == 1) {
-        if (lane < NP) o.rows[(size_t)bid * NP + lane] = s;
+        if (m < M) o.rows[m * kSumDoubles + (size_t)bid * NP + k] = s;
         return false;
     }
-    if (lane < NP) store_coherent(&o.part[(size_t)bid * NP + lane], s);
+    if (m < M) store_coherent(&o.part[(size_t)bid * (M * NP) + lane], s);
     wait_memory();
     const int grp = bid / o.group;
     const int gn = min(o.group, nblk - grp * o.group);
@@ -150,30 +156,31 @@ __device__ bool sum_post(double (&part)[NR], const SumOut& o, int nblk, int bid)
 }
 
 // Stage 2, in wave 0 of a work-group for which sum_post returned true.
-template <int NRHS>
+template <int NRHS, int M>
 __device__ void sum_finish(const SumOut& o, int nblk, int bid)
 {
-    constexpr int NP = sum_stride(NRHS);
-    constexpr int RL = 64 / NP;  // rows per pass: lane = (row, rhs)
+    constexpr int NV = M * sum_stride(NRHS);
+    constexpr int RL = 64 / NV;  // rows per pass: lane = (row, sum, rhs)
     const int lane = threadIdx.x & 63;
     const int grp = bid / o.group;
     const int g0 = grp * o.group;
     const int gn = min(o.group, nblk - g0);
     acquire_agent();
     double v = 0;
-    for (int r0 = lane / NP; r0 < gn; r0 += 8 * RL) {
+    for (int r0 = lane / NV; r0 < gn; r0 += 8 * RL) {
         double x[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {  // all loads in flight
             const int r = r0 + j * RL;
-            x[j] = r < gn ? load_coherent(&o.part[(size_t)(g0 + r) * NP + lane % NP]) : 0.0;
+            x[j] = r < gn ? load_coherent(&o.part[(size_t)(g0 + r) * NV + lane % NV]) : 0.0;
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) v += x[j];
     }
 #pragma unroll
-    for (int off = 32; off >= NP; off >>= 1) v += shfl_xor_d(v, off);
-    if (lane < NP) o.rows[(size_t)grp * NP + lane] = v;
+    for (int off = 32; off >= NV; off >>= 1) v += shfl_xor_d(v, off);
+    constexpr int NP = sum_stride(NRHS);
+    if (lane < NV) o.rows[lane / NP * kSumDoubles + (size_t)grp * NP + lane % NP] = v;
     if (lane == 0) store_coherent(&o.cnt[counter_index(grp)], 0u);
 }
 

@@ -154,10 +154,10 @@ inline int sum_row_count(int nblk, int n)
     return (nblk + g - 1) / g;
 }
 
-// Where a reducing kernel leaves its sum.
+// Where a reducing kernel leaves its sums (one, or two at a time).
 struct SumOut {
-    double* rows;   // [sum_row_count][sum_stride], read by the consumer
-    double* part;   // per-work-group partials (groups of more than one)
+    double* rows;   // [sum_row_count][sum_stride] of each sum, kSumDoubles apart, read by the consumer
+    double* part;   // per-work-group partials (groups of more than one), [work-group][sum][sum_stride]
     uint32_t* cnt;  // group counters (zero between launches)
     int group;      // work-groups per row
 };
@@ -192,7 +192,7 @@ struct CgState {
 
 enum Epi {
     EPI_PLAIN = 0,  // out = D in
-    EPI_NORM = 1,   // t = D_oe p; |t|^2
+    EPI_NORM = 1,   // t = D_oe p; |p|^2 and |t|^2
     EPI_CG = 2,     // alpha from |p|^2, |t|^2; u = D_eo t; q = 4m^2 p - u; x += alpha p; r -= alpha q; |r|^2
     EPI_RESID = 3   // (FP64) r = b - (4m^2 x - D_eo t) for selected rhs; |r|^2
 };
@@ -214,7 +214,7 @@ struct DslashArgs {
     const d2* xh;
     double mass4;  // 4 m^2
     CgState* state;
-    SumOut sum;   // where |t|^2, |r|^2 go
+    SumOut sum;    // where |p|^2 and |t|^2, or |r|^2, go
     SumIn pp, tt;  // EPI_CG: |p|^2 and |t|^2 of this iteration
     int ntiles;
     int remap;
@@ -231,9 +231,6 @@ struct PupdateArgs {
     CgState* dst;        // scalars of this iteration
     SumIn rr;            // |r|^2 of the previous iteration (not with fresh)
     int fresh;           // 1: beta and the masks stand in src as they are
-    SumOut sum;          // where |p|^2 goes
-    int ntiles;
-    int remap;
 };
 
 // One problem of a batched launch: the arguments of its three CG phases and
@@ -248,8 +245,10 @@ struct BatchProb {
     CgState* state[3];  // the host's copy, then the two of the poll block
     int n;
     int nr;
-    int block_start;
+    int block_start;  // of the Dslash launches
     int nblocks;
+    int pup_start;  // of the p-update launch
+    int pup_blocks;
 };
 
 template <typename T>
@@ -280,6 +279,9 @@ inline int phase_of(int j) { return j == 0 ? 0 : (j & 1) ? 1 : 2; }
 // three sums of an iteration (|p|^2, |t|^2, |r|^2), then the partials.
 enum SumSlot { SUM_PP = 0, SUM_TT = 1, SUM_RR = 2, SUM_SLOTS = 3 };
 inline size_t red_doubles(size_t blocks) { return (size_t)SUM_SLOTS * kSumDoubles + blocks * kMaxRhs; }
+// A work-group that leaves two sums covers at least this many sites, so that
+// the partials of Vh / 8 work-groups of one sum hold them.
+inline int least_sites(int n) { return 2 * sum_stride(n); }
 constexpr size_t kRedCounters = (size_t)kCounterLines * kCounterStride;
 static_assert(kSumDoubles <= kCounterLines * kCounterStride, "a counter for every group");
 
@@ -295,10 +297,10 @@ hipError_t launch_dslash_batched_f64(int epi, const BatchTable<double>* tab, int
                                      int bs, int phase, hipStream_t s);
 hipError_t launch_dslash_batched_f32(int epi, int nk, const BatchTable<float>* tab,
                                      int total_blocks, int bs, int phase, hipStream_t s);
-hipError_t launch_pupdate_batched_f64(const BatchTable<double>* tab, int total_blocks, int bs,
-                                      int phase, hipStream_t s);
-hipError_t launch_pupdate_batched_f32(const BatchTable<float>* tab, int total_blocks, int bs,
-                                      int phase, hipStream_t s);
+hipError_t launch_pupdate_batched_f64(const BatchTable<double>* tab, int total_blocks, int phase,
+                                      hipStream_t s);
+hipError_t launch_pupdate_batched_f32(const BatchTable<float>* tab, int total_blocks, int phase,
+                                      hipStream_t s);
 // End of a poll block: folds the last iteration (src, |r|^2 rows) into the
 // host's copy dst, for each of nprob problems.
 struct FoldArgs {
@@ -312,15 +314,10 @@ struct FoldArgs {
 hipError_t launch_fold(const FoldArgs& a, int nprob, hipStream_t s);
 // rhs-per-thread tiles the batched kernels are built for
 inline bool batched_nr_ok(int n, int nr) { return nr == n || (n % 2 == 0 && nr == n / 2); }
-// Streaming p-update for bundles of 1, 2, 4 or 8 rhs (any tile).
-inline bool pupdate_flat_ok(int n) { return n == 1 || n == 2 || n == 4 || n == 8; }
-int pupdate_flat_blocks(int nrhs, int Vh);
-hipError_t launch_pupdate_flat_f64(int nrhs, const PupdateArgs<double>& a, hipStream_t s);
-hipError_t launch_pupdate_flat_f32(int nrhs, const PupdateArgs<float>& a, hipStream_t s);
-hipError_t launch_pupdate_f64(int nrhs, const Tile& t, const PupdateArgs<double>& a,
-                              hipStream_t s);
-hipError_t launch_pupdate_f32(int nrhs, const Tile& t, const PupdateArgs<float>& a,
-                              hipStream_t s);
+// work-groups of a p-update; elem: bytes of a real
+int pupdate_blocks(int nrhs, int Vh, size_t elem);
+hipError_t launch_pupdate_f64(int nrhs, const PupdateArgs<double>& a, hipStream_t s);
+hipError_t launch_pupdate_f32(int nrhs, const PupdateArgs<float>& a, hipStream_t s);
 
 // Elementwise and reduction helpers (blas.hip).
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
