@@ -188,12 +188,7 @@ int check_solve_links(const void* links64, const void* links32, const Lat& lat, 
     return rc;
 }
 
-bool valid_nr(int n, int nr)
-{
-    if (nr < 1 || nr > n || n % nr != 0) return false;
-    const int G = n / nr;
-    return G == 1 || G == 2 || G == 4 || G == 8;
-}
+bool valid_nr(int n, int nr) { return nr >= 1 && nr <= n && n % nr == 0; }
 
 // ---------------------------------------------------------------------------
 // Workspace layout (every region 256-byte aligned).
@@ -237,10 +232,9 @@ size_t ws_layout(const Lat& lat, int n, int mode, int kind, char* base, Ws* w)
     };
     const size_t f64 = (size_t)lat.Vh * 3 * n * sizeof(d2);
     const size_t f32 = (size_t)lat.Vh * 3 * n * sizeof(f2);
-    const size_t maxblocks = (size_t)lat.Vh * 8 / 64 + 1;  // block >= 64 threads, <= 8 per site
     w->st = (CgState*)take(sizeof(CgState));
     w->cs = (CgState*)take(2 * sizeof(CgState));
-    w->red = (double*)take(red_doubles(maxblocks) * sizeof(double));
+    w->red = (double*)take(red_doubles(lat.Vh, n) * sizeof(double));
     w->cnt_bytes = kRedCounters * sizeof(uint32_t);
     w->cnt = (uint32_t*)take(w->cnt_bytes);
     w->r64 = (d2*)take(f64);
@@ -285,13 +279,6 @@ SumIn sum_in(const Ws& w, int slot, int nblk, int n)
 {
     return SumIn{w.red + (size_t)slot * kSumDoubles, sum_row_count(nblk, n)};
 }
-// work-groups of a Dslash (or site-tiled p-update) launch
-int tile_blocks(const Lat& lat, int n, int nr, int bs)
-{
-    const long threads = (long)lat.Vh * (n / nr);
-    return (int)((threads + bs - 1) / bs);
-}
-int tile_blocks(const Lat& lat, int n, const Tile& t) { return tile_blocks(lat, n, t.nr, t.bs); }
 
 // ---------------------------------------------------------------------------
 // Packed link access.
@@ -335,18 +322,13 @@ int g_force_eo_nr = 0, g_force_eo_bs = 0, g_force_eo_order = 1, g_force_eo_rows 
 
 // Tile order 2 needs tiles that never straddle a time slice; order 3 needs
 // z-chunks of whole planes for each of the 8 XCDs and tiles that divide an x-y
-// plane.
-bool t_order_ok(const Lat& lat, int G, int bs, int order)
+// plane.  Split tiles run in canonical order (their launches are one pass).
+bool t_order_ok(const Lat& lat, int n, const Tile& t, int order)
 {
-    if (order == 2) {
-        const long slice_threads = (long)lat.Vh / lat.L[3] * G;
-        return slice_threads % bs == 0;
-    }
-    if (order == 3) {
-        const int tile_sites = bs / G;
-        const int plane = lat.L[0] * lat.L[1] / 2;
-        return bs % G == 0 && lat.L[2] % 8 == 0 && plane % tile_sites == 0;
-    }
+    if (t.split) return order == 0;
+    const int ts = tile_sites(n, t);
+    if (order == 2) return lat.Vh / lat.L[3] % ts == 0;
+    if (order == 3) return lat.L[2] % 8 == 0 && lat.L[0] * lat.L[1] / 2 % ts == 0;
     return order == 0 || order == 1;
 }
 
@@ -357,6 +339,7 @@ bool t_order_ok(const Lat& lat, int G, int bs, int order)
 int staged_block(const Lat& lat, int n, int G, int R, int prec)
 {
     if (R < 1) return 0;
+    if (64 % G != 0) return 0;
     const long bs = (long)R * lat.Lh0 * G;
     const size_t elt = prec == HISQ_PREC_F64 ? 16 : 8;
     const size_t lds = (size_t)3 * (R + 6) * lat.Lh0 * n * elt;
@@ -375,6 +358,21 @@ Tile default_tile(int n, int prec)
                 break;
             }
     }
+    return t;
+}
+
+// The split Dslash (four lanes per site and rhs) is for launches that do not
+// fill the chip: up to `waves` x 8 waves per SIMD of its own.
+bool small_launch(const Lat& lat, int n, int waves)
+{
+    return (long)lat.Vh * n * 4 <= (long)waves * 256 * 4 * 8 * 64;
+}
+
+Tile split_tile(int n)
+{
+    Tile t{1, 64, 0};
+    t.split = 1;
+    while (tile_sites(n, t) < kLeastSites) t.bs *= 2;
     return t;
 }
 
@@ -403,19 +401,20 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
         ford = eo ? g_force_eo_order : g_force_order;
         frows = eo ? g_force_eo_rows : g_force_rows;
     }
-    // a reducing kernel's work-group covers at least least_sites(n) sites
-    auto enough = [&](int nr, int bs) { return epi == EPI_PLAIN || bs / (n / nr) >= least_sites(n); };
+    // a reducing kernel's work-group covers at least kLeastSites sites
+    auto enough = [&](const Tile& c) { return epi == EPI_PLAIN || tile_sites(n, c) >= kLeastSites; };
     if (mode == 1 && valid_nr(n, fnr)) {
         int sbs = cm ? staged_block(lat, n, n / fnr, frows, prec) : 0;
-        if (sbs && !enough(fnr, sbs)) sbs = 0;
-        while (!enough(fnr, fbs)) fbs *= 2;
+        if (sbs && !enough(Tile{fnr, sbs, 0})) sbs = 0;
+        while (!enough(Tile{fnr, fbs, 0})) fbs *= 2;
         Tile t{fnr, sbs ? sbs : fbs, ford, sbs ? frows : 0};
-        if (!t_order_ok(lat, n / fnr, t.bs, t.remap)) t.remap = 1;
+        if (!t_order_ok(lat, n, t, t.remap)) t.remap = 1;
         *out = t;
         return HISQ_OK;
     }
     if (mode != 0) {
         *out = default_tile(n, prec);
+        if (cm && (epi == EPI_NORM || epi == EPI_CG) && small_launch(lat, n, 1)) *out = split_tile(n);
         return HISQ_OK;
     }
     const std::string key = tune_key(lat, n, prec, nk, epi, cm);
@@ -437,22 +436,25 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
     // candidates: unstaged tiles of 64, 128, 256 threads, then (colour-major
     // only) LDS-staged tiles of 1..16 rows
     std::vector<Tile> cand;
-    for (int G = 1; G <= 8; G *= 2) {
+    for (int G = 1; G <= n; ++G) {
         if (n % G != 0) continue;
         for (int bs : {64, 128, 256})
-            if (enough(n / G, bs)) cand.push_back(Tile{n / G, bs, 0, 0});
+            if (enough(Tile{n / G, bs, 0})) cand.push_back(Tile{n / G, bs, 0, 0});
         if (cm)
             for (int R = 1; R <= 16; ++R) {
                 const int sbs = staged_block(lat, n, G, R, prec);
-                if (sbs && enough(n / G, sbs)) cand.push_back(Tile{n / G, sbs, 0, R});
+                if (sbs && enough(Tile{n / G, sbs, 0})) cand.push_back(Tile{n / G, sbs, 0, R});
             }
     }
+    if (cm && (epi == EPI_NORM || epi == EPI_CG) && small_launch(lat, n, 2)) {
+        Tile c = split_tile(n);
+        for (; c.bs <= kMaxBlock; c.bs *= 2) cand.push_back(c);
+    }
     for (const Tile& base : cand) {
-        const int G = n / base.nr;
         for (int remap = 0; remap < 4; ++remap) {
                 Tile c = base;
                 c.remap = remap;
-                if (!t_order_ok(lat, G, c.bs, remap)) continue;
+                if (!t_order_ok(lat, n, c, remap)) continue;
                 if (launch_ds(epi, n, nk, c, probe, s, cm) != hipSuccess) continue;
                 HIP_TRY(hipEventRecord(e0, s));
                 for (int rep = 0; rep < 3; ++rep) HIP_TRY(launch_ds(epi, n, nk, c, probe, s, cm));
@@ -702,7 +704,7 @@ struct Engine {
         const int last = state_of_phase(phase_of(iters - 1), 1);
         for (size_t j = 0; j < P.size(); ++j) {
             const Prob& q = P[j];
-            const int nb3 = P.size() > 1 ? tile_blocks(q.lat, q.n, batch_nr(q), batch_bs)
+            const int nb3 = P.size() > 1 ? tile_blocks(q.lat, q.n, Tile{batch_nr(q), batch_bs, 0})
                                          : tile_blocks(q.lat, q.n, mixed ? q.t32e : q.t64e);
             f.p[j] = FoldArgs::One{state_copy(q, last), q.w.st, sum_in(q.w, SUM_RR, nb3, q.n), q.n};
         }
@@ -727,7 +729,7 @@ struct Engine {
             BatchProb<T>& bp = tab->p[jj];
             bp.n = q.n;
             bp.nr = batch_nr(q);
-            bp.nblocks = tile_blocks(q.lat, q.n, bp.nr, bs);
+            bp.nblocks = tile_blocks(q.lat, q.n, Tile{bp.nr, bs, 0});
             iter_args<T>(q, bp.k1, bp.k2, bp.k3, 0, bp.nblocks, bp.nblocks);
             bp.pup_blocks = pupdate_blocks(q.n, q.lat.Vh, sizeof(T));
             bp.pup_start = pup;
@@ -736,8 +738,7 @@ struct Engine {
             for (int c = 0; c < 3; ++c) bp.state[c] = state_copy(q, tuning ? 0 : c);
             // XCD-owned z-chunks where the problem's tiles allow, else one
             // contiguous slab per XCD
-            const int G = q.n / bp.nr;
-            bp.k2.remap = bp.k3.remap = t_order_ok(q.lat, G, bs, 3) ? 3 : 1;
+            bp.k2.remap = bp.k3.remap = t_order_ok(q.lat, q.n, Tile{bp.nr, bs, 0}, 3) ? 3 : 1;
             bp.k2.ntiles = bp.k3.ntiles = bp.nblocks;
             bp.block_start = start;
             start += bp.nblocks;

@@ -103,6 +103,15 @@ __device__ __forceinline__ void apply_slot(cplx<T> (&m)[9], const cplx<T> (&v)[3
             for (int k = 0; k < NR; ++k) cfma(acc[a][k], m[3 * a + b], v[b][k]);
 }
 
+// lanes that share one site's link loads: the site's lanes, quads when there are
+// 8, none when their number is not a power of two (they do not fill quads)
+template <int NRHS, int NR>
+constexpr int link_group()
+{
+    constexpr int G = NRHS / NR;
+    return G == 1 || G == 2 || G == 4 ? G : G == 8 ? 4 : 1;
+}
+
 // Pipeline step k -> slot: even steps take the z and t slots, odd steps the x
 // and y slots, hops +1, -1, +3, -3 within each direction.  The LDS-staged
 // kernel reads the x and y neighbours from LDS and overlaps them with the
@@ -161,8 +170,7 @@ __device__ __forceinline__ void dslash_site(const Lat& lat, int P, int i, int g,
 #define HISQ_FP32_LINK_LOOKAHEAD 1
 #endif
     constexpr int LD = sizeof(T) == 4 ? HISQ_FP32_LINK_LOOKAHEAD : 1;
-    // lanes sharing a link: the site's lanes, in quads when there are 8
-    constexpr int G = (NRHS / NR) < 4 ? NRHS / NR : 4;
+    constexpr int G = link_group<NRHS, NR>();
     const int gl = g % G;
     LinkRaw<T, G> lr[LD + 1];
     C v[2][3][NR];
@@ -184,6 +192,86 @@ __device__ __forceinline__ void dslash_site(const Lat& lat, int P, int i, int g,
         __builtin_amdgcn_sched_barrier(0);
     });
     if constexpr (PN) own_norm<T, NR>(v[0], own);
+}
+
+// ---------------------------------------------------------------------------
+// Split form, for launches too small to fill the chip: four adjacent lanes share
+// a site and its rhs tile, lane mu takes the four hops of direction mu, issues
+// all their loads at once and the quad adds the four partial results with DPP
+// permutes.  A wave then waits for one memory round trip instead of 16 in a
+// row, and there are four times as many waves.
+// 8^4, FP64, one rhs: a solve takes 2.87 ms on these kernels, 3.73 ms on the
+// sequential ones; where the sequential tiles fill the chip (from about 8 waves
+// per SIMD) four lanes only repeat the index arithmetic.
+template <typename T, int NK, int HH>
+__device__ __forceinline__ void load_link_dir(const cplx<T>* __restrict__ lk, int Vh, int i, int mu,
+                                              cplx<T> (&m)[9])
+{
+    // as load_link, for slot 4 * HH + mu
+    constexpr int nr = slot_reals(4 * HH, NK);
+    const T* base = reinterpret_cast<const T*>(lk) +
+                    (size_t)(slot_real_start(4 * HH, NK) + mu * nr) * Vh;
+    if constexpr (sizeof(T) == 4) {
+        constexpr int nw = nr / 4, rem = nr % 4;
+        const f4* wp = reinterpret_cast<const f4*>(base) + i;
+#pragma unroll
+        for (int w = 0; w < nw; ++w) {
+            const f4 q = __builtin_nontemporal_load(wp + (size_t)w * Vh);
+            m[2 * w] = cplx<T>{q.x, q.y};
+            m[2 * w + 1] = cplx<T>{q.z, q.w};
+        }
+        const T* tail = base + (size_t)4 * nw * Vh;
+        if constexpr (rem == 2)
+            m[2 * nw] = __builtin_nontemporal_load(reinterpret_cast<const cplx<T>*>(tail) + i);
+        else if constexpr (rem == 1)
+            m[2 * nw] = cplx<T>{__builtin_nontemporal_load(tail + i), T(0)};
+    } else {
+        const cplx<T>* lp = reinterpret_cast<const cplx<T>*>(base) + i;
+#pragma unroll
+        for (int e = 0; e < 9; ++e) m[e] = __builtin_nontemporal_load(lp + (size_t)e * Vh);
+    }
+}
+
+template <typename T, int NRHS, int NR, int NK>
+__device__ __forceinline__ void dslash_site_split(const Lat& lat, int P, int i, int g, int mu,
+                                                  const cplx<T>* __restrict__ lk,
+                                                  const cplx<T>* __restrict__ in,
+                                                  cplx<T> (&acc)[3][NR], T ns)
+{
+    using C = cplx<T>;
+    const SiteCoord sc = site_coord(lat, P, i);
+    // scalar registers first: a select between members of the argument struct
+    // becomes an indexed load from a copy of it in scratch memory
+    auto scalar = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    const int l0 = scalar(lat.L[0]), l1 = scalar(lat.L[1]), l2 = scalar(lat.L[2]), l3 = scalar(lat.L[3]);
+    const int s1 = scalar(lat.sy), s2 = scalar(lat.sz), s3 = scalar(lat.st);
+    const int c = mu == 0 ? sc.x : mu == 1 ? sc.c[1] : mu == 2 ? sc.c[2] : sc.c[3];
+    const int ext = mu == 0 ? l0 : mu == 1 ? l1 : mu == 2 ? l2 : l3;
+    const int stride = mu == 1 ? s1 : mu == 2 ? s2 : s3;
+    C m[4][9], v[4][3][NR];
+    static_for<0, 4>([&](auto H) {
+        constexpr int hh = decltype(H)::value;
+        constexpr int h = hh == 0 ? 1 : hh == 1 ? -1 : hh == 2 ? 3 : -3;
+        const int d = wrap_delta(c, h, ext);
+        const int nbr = mu == 0 ? sc.row + ((c + d) >> 1) : i + d * stride;
+        load_vec<T, NRHS, NR, true>(in, lat.Vh, nbr, g, v[hh]);
+        load_link_dir<T, NK, hh>(lk, lat.Vh, i, mu, m[hh]);
+    });
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int k = 0; k < NR; ++k) acc[a][k] = C{0, 0};
+    static_for<0, 4>([&](auto H) {
+        constexpr int hh = decltype(H)::value;
+        apply_slot<T, NR, NK, 4 * hh>(m[hh], v[hh], acc, ns);
+    });
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            acc[a][k].x = quad_sum(acc[a][k].x);
+            acc[a][k].y = quad_sum(acc[a][k].y);
+        }
 }
 
 // ---------------------------------------------------------------------------
@@ -310,10 +398,6 @@ __device__ __forceinline__ int lds_neighbour(const Lat& lat, int r, int xh, int 
 // The global reads that open the pipeline (slot 0's link, the first two
 // global neighbours): issued before the work-group's staging barrier, so
 // that their latency overlaps the staging reads instead of following them.
-// lanes that share one site's link loads (quads when a site has 8 lanes)
-template <int NRHS, int NR>
-constexpr int link_group() { return (NRHS / NR) < 4 ? NRHS / NR : 4; }
-
 template <typename T, int NRHS, int NR, int NK>
 struct LdsHead {
     LinkRaw<T, link_group<NRHS, NR>()> m;
@@ -405,12 +489,13 @@ __device__ __forceinline__ void pin_acc(C (&acc)[3][NR])
 // One tile (one work-group's worth of sites) of a half-Dslash with epilogue
 // EPI; `tile` is the tile index, the problem's grid has nblk work-groups and
 // this one is number bid (for the reductions).
-template <typename T, int NRHS, int NR, int NK, int EPI, bool CM, bool ST = false>
+template <typename T, int NRHS, int NR, int NK, int EPI, bool CM, bool ST = false, int SPL = 1>
 __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* state, int tile,
                                             int nblk, int bid, cplx<T>* lds = nullptr)
 {
     using C = cplx<T>;
-    constexpr int G = NRHS / NR;
+    using Map = LaneMap<NRHS, NR, SPL>;
+    constexpr int G = Map::G;
     if constexpr (EPI == EPI_NORM || EPI == EPI_CG) {
         // every rhs of the bundle converged: the iteration is a no-op
         bool any_prob = false;
@@ -418,7 +503,8 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
         for (int k = 0; k < NRHS; ++k) any_prob = any_prob || (state->active[k] != 0);
         if (!any_prob) return;
     }
-    const int g = threadIdx.x % G;
+    const int g = Map::group();
+    const int mu = Map::dir();  // split form: this lane's direction, then its colour
     constexpr int M = EPI == EPI_NORM ? 2 : 1;  // |p|^2 and |t|^2, or one sum
     double part[M][NR];
 #pragma unroll
@@ -440,7 +526,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
     T ns = T(1);  // r9: the Naik scale of the links
     if constexpr (NK == HISQ_NAIK_R9) ns = (T)*a.naik_scale;
 
-    const int i = (tile * (int)blockDim.x + (int)threadIdx.x) / G;
+    const int i = Map::site(tile);
     LdsHead<T, NRHS, NR, NK> head;
     if constexpr (ST) {
         // the tile is `rows` whole x-rows: stage them and their +-3 row halo
@@ -453,14 +539,27 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
     // work-group's reduction partials, and only then stores the outputs: the
     // completion wait that orders the partials before the counter update does
     // not wait for the output stores.
-    const bool on_site = i < a.lat.Vh;
+    bool on_site = Map::live() && i < a.lat.Vh;
     using Lay = Layout<NRHS, CM>;
     const int base = Lay::site(on_site ? i : 0) + g * NR;
+    constexpr int NC = SPL == 1 ? 3 : 1;  // colours this lane stores
     C acc[3][NR];
-    C xo[3][NR], ro[3][NR];  // EPI_CG: updated x and r
-    d2 rr[3][NR];            // EPI_RESID: the FP64 residual
+    C xo[NC][NR], ro[NC][NR];  // EPI_CG: updated x and r
+    d2 rr[NC][NR];             // EPI_RESID: the FP64 residual
+    auto colour = [&](int c) { return base + Lay::colour(SPL == 1 ? c : mu, a.lat.Vh); };
     if (on_site) {
-        if constexpr (ST)
+        if constexpr (SPL > 1) {
+            static_assert(CM && !ST, "split form: colour-major fields, not staged");
+            C pv[NR];
+            if constexpr (EPI == EPI_NORM) load_rhs<NR>(a.in + base + Lay::colour(mu < 3 ? mu : 0, a.lat.Vh), pv);
+            dslash_site_split<T, NRHS, NR, NK>(a.lat, a.parity, i, g, mu, a.links, a.in, acc, ns);
+            if constexpr (EPI == EPI_NORM) {
+#pragma unroll
+                for (int k = 0; k < NR; ++k) part[0][k] = mu < 3 ? norm2c<T>(pv[k]) : 0.0;
+            }
+#pragma unroll
+            for (int k = 0; k < NR; ++k) acc[0][k] = mu == 0 ? acc[0][k] : mu == 1 ? acc[1][k] : acc[2][k];
+        } else if constexpr (ST)
             dslash_site_lds<T, NRHS, NR, NK, EPI == EPI_NORM>(
                 a.lat, a.parity, i, g, ((int)threadIdx.x / G) / a.lat.Lh0, a.links, a.in, lds,
                 a.rows + 6, head, acc, ns, part[0]);
@@ -469,6 +568,8 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
                                                               acc, ns, part[0]);
         pin_acc(acc);
     }
+    // split form: lanes 0..2 of a quad each store one colour
+    if constexpr (SPL > 1) on_site = on_site && mu < 3;
     if constexpr (EPI == EPI_CG) {
         // alpha = rr / <p, A p>, with <p, A p> = 4m^2 |p|^2 + |D_oe p|^2
         // (D_eo^dag = -D_oe), for rhs lane mod NP in every wave; a rhs whose
@@ -492,7 +593,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
     if (on_site) {
         if constexpr (EPI == EPI_NORM) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
+            for (int c = 0; c < NC; ++c)
 #pragma unroll
                 for (int k = 0; k < NR; ++k) part[M - 1][k] += norm2c<T>(acc[c][k]);
         } else if constexpr (EPI == EPI_CG) {
@@ -501,11 +602,11 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
             // whole tile of the thread is masked); their partial sums stay
             // zero and their finisher ignores them
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
+            for (int c = 0; c < NC; ++c) {
                 C pv[NR];
-                load_rhs<NR, true>(a.p + base + Lay::colour(c, a.lat.Vh), pv);
-                load_rhs<NR, true>(a.x + base + Lay::colour(c, a.lat.Vh), xo[c]);
-                load_rhs<NR, true>(a.r + base + Lay::colour(c, a.lat.Vh), ro[c]);
+                load_rhs<NR, true>(a.p + colour(c), pv);
+                load_rhs<NR, true>(a.x + colour(c), xo[c]);
+                load_rhs<NR, true>(a.r + colour(c), ro[c]);
 #pragma unroll
                 for (int k = 0; k < NR; ++k) {
                     const C q = C{m4 * pv[k].x - acc[c][k].x, m4 * pv[k].y - acc[c][k].y};
@@ -518,10 +619,10 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
         } else if constexpr (EPI == EPI_RESID) {
             if (any_act) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
+            for (int c = 0; c < NC; ++c) {
                 d2 bv[NR], xv[NR];
-                load_rhs<NR>(a.b + base + Lay::colour(c, a.lat.Vh), bv);
-                load_rhs<NR>(a.xh + base + Lay::colour(c, a.lat.Vh), xv);
+                load_rhs<NR>(a.b + colour(c), bv);
+                load_rhs<NR>(a.xh + colour(c), xv);
 #pragma unroll
                 for (int k = 0; k < NR; ++k) {
                     rr[c][k] = d2{bv[k].x - (m4 * xv[k].x - acc[c][k].x),
@@ -534,27 +635,27 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
     }
 
     bool last = false;
-    if constexpr (EPI != EPI_PLAIN) last = sum_post<NRHS, NR, M>(part, a.sum, nblk, bid);
+    if constexpr (EPI != EPI_PLAIN) last = sum_post<NRHS, NR, M, SPL>(part, a.sum, nblk, bid);
 
     if (on_site) {
         if constexpr (EPI == EPI_PLAIN || EPI == EPI_NORM) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) store_rhs<NR>(a.out + base + Lay::colour(c, a.lat.Vh), acc[c]);
+            for (int c = 0; c < NC; ++c) store_rhs<NR>(a.out + colour(c), acc[c]);
         } else if constexpr (EPI == EPI_CG) {
             if (any_act) {
                 // plain stores: L2 merges the partial lines of consecutive
                 // store instructions before they reach HBM
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    store_rhs_on<NR>(a.x + base + Lay::colour(c, a.lat.Vh), xo[c], act);
-                    store_rhs_on<NR>(a.r + base + Lay::colour(c, a.lat.Vh), ro[c], act);
+                for (int c = 0; c < NC; ++c) {
+                    store_rhs_on<NR>(a.x + colour(c), xo[c], act);
+                    store_rhs_on<NR>(a.r + colour(c), ro[c], act);
                 }
             }
         } else if constexpr (EPI == EPI_RESID) {
             if (any_act) {
 #pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    store_rhs_on<NR>(a.out + base + Lay::colour(c, a.lat.Vh), rr[c], act);
+                for (int c = 0; c < NC; ++c)
+                    store_rhs_on<NR>(a.out + colour(c), rr[c], act);
             }
         }
     }
@@ -570,10 +671,16 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
 #define HISQ_KATTR
 #endif
 
+template <typename T, int NRHS, int NR, int NK, int EPI>
+__global__ __launch_bounds__(kMaxBlock) void k_dslash_split(const DslashArgs<T> a)
+{
+    dslash_tile<T, NRHS, NR, NK, EPI, true, false, 4>(a, a.state, blockIdx.x, gridDim.x, blockIdx.x);
+}
+
 template <typename T, int NRHS, int NR, int NK, int EPI, bool CM>
 __global__ __launch_bounds__(kMaxBlock) HISQ_KATTR void k_dslash(const DslashArgs<T> a)
 {
-    const int tile_sites = (int)blockDim.x / (NRHS / NR);
+    const int tile_sites = LaneMap<NRHS, NR, 1>::sites(blockDim.x);
     dslash_tile<T, NRHS, NR, NK, EPI, CM>(
         a, a.state, tile_of_block(blockIdx.x, gridDim.x, a.remap, a.lat, tile_sites), gridDim.x, blockIdx.x);
 }
@@ -626,22 +733,34 @@ __global__ __launch_bounds__(kMaxBlock) void k_dslash_batched(const BatchTable<T
 template <typename T, int NK, int EPI, int NRHS, int NR>
 static hipError_t go(const Tile& t, DslashArgs<T> a, hipStream_t s, bool cm)
 {
-    constexpr int G = NRHS / NR;
-    const long threads = (long)a.lat.Vh * G;
-    a.ntiles = (int)((threads + t.bs - 1) / t.bs);
+    a.ntiles = tile_blocks(a.lat, NRHS, t);
     a.remap = t.remap;
     a.rows = t.rows;
     // each kernel is built for a maximum work-group size; the grid
     // reductions need whole waves
     if (t.bs < 64 || t.bs % 64 != 0 || t.bs > (t.rows > 0 ? kMaxBlockLds : kMaxBlock))
         return hipErrorInvalidValue;
+    if (t.split) {
+        // one rhs per lane, the kernels of a solve
+        if constexpr (NR == 1 && (EPI == EPI_NORM || EPI == EPI_CG || sizeof(T) == 8)) {
+            if (!cm || t.rows > 0) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((k_dslash_split<T, NRHS, NR, NK, EPI>), dim3(a.ntiles), dim3(t.bs), 0, s, a);
+            return hipGetLastError();
+        } else {
+            return hipErrorInvalidValue;
+        }
+    }
     if (t.rows > 0) {
         // LDS-staged: colour-major only; the host has checked that a tile is
         // t.rows whole x-rows of one plane and that the rows fit in LDS
         if (!cm) return hipErrorInvalidValue;
         const size_t lds = (size_t)3 * (t.rows + 6) * a.lat.Lh0 * NRHS * sizeof(cplx<T>);
-        hipLaunchKernelGGL((k_dslash_lds<T, NRHS, NR, NK, EPI>), dim3(a.ntiles), dim3(t.bs), lds, s, a);
-        return hipGetLastError();
+        if constexpr (64 % (NRHS / NR) == 0) {
+            hipLaunchKernelGGL((k_dslash_lds<T, NRHS, NR, NK, EPI>), dim3(a.ntiles), dim3(t.bs), lds, s, a);
+            return hipGetLastError();
+        } else {
+            return hipErrorInvalidValue;
+        }
     }
     // the solver's kernels exist in colour-major form only; the plain Dslash in both
     if (cm)
@@ -656,13 +775,16 @@ static hipError_t go(const Tile& t, DslashArgs<T> a, hipStream_t s, bool cm)
 template <typename T, int NK, int EPI, int NRHS>
 static hipError_t pick_nr(const Tile& t, const DslashArgs<T>& a, hipStream_t s, bool cm)
 {
+    // every divisor of the bundle
     if (t.nr == NRHS) return go<T, NK, EPI, NRHS, NRHS>(t, a, s, cm);
-    if constexpr (NRHS % 2 == 0)
+    if constexpr (NRHS % 2 == 0 && NRHS > 2)
         if (t.nr == NRHS / 2) return go<T, NK, EPI, NRHS, NRHS / 2>(t, a, s, cm);
-    if constexpr (NRHS % 4 == 0)
-        if (t.nr == NRHS / 4) return go<T, NK, EPI, NRHS, NRHS / 4>(t, a, s, cm);
-    if constexpr (NRHS % 8 == 0)
-        if (t.nr == NRHS / 8) return go<T, NK, EPI, NRHS, NRHS / 8>(t, a, s, cm);
+    if constexpr (NRHS % 3 == 0 && NRHS > 3)
+        if (t.nr == NRHS / 3) return go<T, NK, EPI, NRHS, NRHS / 3>(t, a, s, cm);
+    if constexpr (NRHS == 8)
+        if (t.nr == 2) return go<T, NK, EPI, NRHS, 2>(t, a, s, cm);
+    if constexpr (NRHS > 1)
+        if (t.nr == 1) return go<T, NK, EPI, NRHS, 1>(t, a, s, cm);
     return hipErrorInvalidValue;
 }
 

@@ -265,7 +265,17 @@ struct Tile {
     int bs;
     int remap;
     int rows = 0;  // > 0: LDS-staged Dslash, the work-group covers `rows` x-rows
+    int split = 0;  // 1: four lanes per site and rhs, one per direction (nr = 1)
 };
+
+// Sites per work-group and work-groups of a Dslash launch of n rhs: a wave holds
+// as many whole sites as its 64 lanes allow.
+inline int tile_sites(int n, const Tile& t) { return t.bs / 64 * (64 / (n / t.nr * (t.split ? 4 : 1))); }
+inline int tile_blocks(const Lat& lat, int n, const Tile& t)
+{
+    const int ts = tile_sites(n, t);
+    return (lat.Vh + ts - 1) / ts;
+}
 
 // Iteration j of a poll block runs in phase 0 (j = 0), 1 (j odd) or 2 (j even):
 // it reads the copy state_of_phase(phase, 0) and writes state_of_phase(phase, 1).
@@ -278,10 +288,12 @@ inline int phase_of(int j) { return j == 0 ? 0 : (j & 1) ? 1 : 2; }
 // Reduction scratch for a grid of up to `blocks` work-groups: the rows of the
 // three sums of an iteration (|p|^2, |t|^2, |r|^2), then the partials.
 enum SumSlot { SUM_PP = 0, SUM_TT = 1, SUM_RR = 2, SUM_SLOTS = 3 };
-inline size_t red_doubles(size_t blocks) { return (size_t)SUM_SLOTS * kSumDoubles + blocks * kMaxRhs; }
-// A work-group that leaves two sums covers at least this many sites, so that
-// the partials of Vh / 8 work-groups of one sum hold them.
-inline int least_sites(int n) { return 2 * sum_stride(n); }
+// Every reducing work-group covers at least kLeastSites sites and leaves at most two sums.
+constexpr int kLeastSites = 8;
+inline size_t red_doubles(int Vh, int n)
+{
+    return (size_t)SUM_SLOTS * kSumDoubles + ((size_t)Vh / kLeastSites + 1) * 2 * sum_stride(n);
+}
 constexpr size_t kRedCounters = (size_t)kCounterLines * kCounterStride;
 static_assert(kSumDoubles <= kCounterLines * kCounterStride, "a counter for every group");
 

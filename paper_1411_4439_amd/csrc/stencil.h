@@ -129,6 +129,34 @@ __device__ __forceinline__ f4 group_bcast4(f4 v)
     }
 }
 
+// Value of the lane with quad index ^ X (X = 1 or 2).
+template <int X>
+__device__ __forceinline__ float quad_xor(float v)
+{
+    constexpr int ctrl = X == 1 ? 0xB1 : 0x4E;  // quad_perm [1,0,3,2], [2,3,0,1]
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, 0xF, 0xF, false));
+}
+template <int X>
+__device__ __forceinline__ double quad_xor(double v)
+{
+    constexpr int ctrl = X == 1 ? 0xB1 : 0x4E;
+    union {
+        double d;
+        int w[2];
+    } u{v};
+    u.w[0] = __builtin_amdgcn_update_dpp(0, u.w[0], ctrl, 0xF, 0xF, false);
+    u.w[1] = __builtin_amdgcn_update_dpp(0, u.w[1], ctrl, 0xF, 0xF, false);
+    return u.d;
+}
+// Sum over the four lanes of a quad, the same bits in each.  All four active.
+template <typename T>
+__device__ __forceinline__ T quad_sum(T v)
+{
+    v += quad_xor<1>(v);
+    return v + quad_xor<2>(v);
+}
+
 // Issue this lane's share of the loads of slot S (lane g of its group).
 template <typename T, int NK, int S, int G>
 __device__ __forceinline__ void load_link_part(const cplx<T>* __restrict__ lk, int Vh, int i, int g,
