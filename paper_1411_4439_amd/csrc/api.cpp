@@ -361,12 +361,13 @@ Tile default_tile(int n, int prec)
     return t;
 }
 
-// The split Dslash (four lanes per site and rhs) is for launches that do not
-// fill the chip: up to `waves` x 8 waves per SIMD of its own.
-bool small_launch(const Lat& lat, int n, int waves)
-{
-    return (long)lat.Vh * n * 4 <= (long)waves * 256 * 4 * 8 * 64;
-}
+// The split Dslash (four lanes per site and rhs) is for the smallest launches,
+// up to 32k lanes of its own (half a wave per SIMD): 8^4, one rhs (8k lanes),
+// 2.7 ms a solve against 3.5 ms on one rhs per lane; 12^3 x 6, 4 rhs (83k)
+// 9.6 against 8.2 ms, 16^3 x 4, 3 rhs (98k) 10.2 against 8.6 ms: there every rhs
+// repeats the link loads of its site.  The autotuner tries it up to four times that.
+constexpr long kSplitLanes = 32768;
+bool small_launch(const Lat& lat, int n, int times) { return (long)lat.Vh * n * 4 <= times * kSplitLanes; }
 
 Tile split_tile(int n)
 {
@@ -446,7 +447,7 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
                 if (sbs && enough(Tile{n / G, sbs, 0})) cand.push_back(Tile{n / G, sbs, 0, R});
             }
     }
-    if (cm && (epi == EPI_NORM || epi == EPI_CG) && small_launch(lat, n, 2)) {
+    if (cm && (epi == EPI_NORM || epi == EPI_CG) && small_launch(lat, n, 4)) {
         Tile c = split_tile(n);
         for (; c.bs <= kMaxBlock; c.bs *= 2) cand.push_back(c);
     }
@@ -554,6 +555,19 @@ struct Engine {
     double kms[HISQ_K_COUNT] = {};
     int klaunch[HISQ_K_COUNT] = {};
     int updates = 0, polls = 0;
+    std::vector<int> live;  // problems with a rhs still running: what a poll block launches
+
+    // The one problem whose own kernels a poll block runs, or NULL: a single
+    // solve's, or the last of a batch where one rhs per lane does not fill the
+    // chip (latency-bound launches: 158 iterations of 16^3 x 4, 3 rhs, at the end
+    // of six solves).
+    const Prob* solo() const
+    {
+        if (P.size() == 1) return &P[0];
+        if (live.size() != 1) return nullptr;
+        const Prob& q = P[live[0]];
+        return small_launch(q.lat, q.n, 4) ? &q : nullptr;
+    }
 
     DslashArgs<double> args64(const Prob& q, int parity) const
     {
@@ -644,14 +658,21 @@ struct Engine {
         k3.r = r;
     }
 
+    // Tile of the solo problem's D_oe or D_eo kernel.
+    Tile solo_tile(bool eo) const
+    {
+        const Prob& q = *solo();
+        if (P.size() > 1) return small_launch(q.lat, q.n, 1) ? split_tile(q.n) : Tile{1, 256, 0};
+        return eo ? (mixed ? q.t32e : q.t64e) : (mixed ? q.t32 : q.t64);
+    }
+
     template <typename T>
     int emit_single(hipStream_t st, int phase, hipEvent_t* evs)
     {
-        const Prob& q = P[0];
+        const Prob& q = *solo();
         PupdateArgs<T> k1;
         DslashArgs<T> k2, k3;
-        const Tile& tile = std::is_same<T, float>::value ? q.t32 : q.t64;
-        const Tile& tile_e = std::is_same<T, float>::value ? q.t32e : q.t64e;
+        const Tile tile = solo_tile(false), tile_e = solo_tile(true);
         iter_args<T>(q, k1, k2, k3, phase, tile_blocks(q.lat, q.n, tile),
                      tile_blocks(q.lat, q.n, tile_e));
         const int rr = std::is_same<T, float>::value ? nk : HISQ_NAIK_FULL;
@@ -693,7 +714,7 @@ struct Engine {
             hipEvent_t* evs = with_events ? &ev[4 * j] : nullptr;
             const int ph = phase_of(j);
             int rc;
-            if (P.size() == 1)
+            if (solo())
                 rc = mixed ? emit_single<float>(st, ph, evs) : emit_single<double>(st, ph, evs);
             else
                 rc = mixed ? emit_batched<float>(st, ph, evs) : emit_batched<double>(st, ph, evs);
@@ -702,13 +723,13 @@ struct Engine {
         // the last iteration's |r|^2 and scalars into the host's copies
         FoldArgs f{};
         const int last = state_of_phase(phase_of(iters - 1), 1);
-        for (size_t j = 0; j < P.size(); ++j) {
-            const Prob& q = P[j];
-            const int nb3 = P.size() > 1 ? tile_blocks(q.lat, q.n, Tile{batch_nr(q), batch_bs, 0})
-                                         : tile_blocks(q.lat, q.n, mixed ? q.t32e : q.t64e);
-            f.p[j] = FoldArgs::One{state_copy(q, last), q.w.st, sum_in(q.w, SUM_RR, nb3, q.n), q.n};
+        for (size_t j = 0; j < live.size(); ++j) {
+            const Prob& q = P[live[j]];
+            const Tile te = solo() ? solo_tile(true) : Tile{batch_nr(q), batch_bs, 0};
+            f.p[j] = FoldArgs::One{state_copy(q, last), q.w.st,
+                                   sum_in(q.w, SUM_RR, tile_blocks(q.lat, q.n, te), q.n), q.n};
         }
-        HIP_TRY(launch_fold(f, (int)P.size(), st));
+        HIP_TRY(launch_fold(f, (int)live.size(), st));
         return HISQ_OK;
     }
 
@@ -780,8 +801,10 @@ struct Engine {
     {
         if (prm.poll_every > 0) return prm.poll_every;
         double bytes = 0;
-        for (const Prob& q : P)
+        for (int j : live) {
+            const Prob& q = P[j];
             bytes += (double)q.lat.Vh * (mixed ? (2304.0 + 264.0 * q.n) : (4608.0 + 528.0 * q.n));
+        }
         const double est = bytes / 4.0e12 + 3 * 4.0e-6;
         const int k = (int)std::ceil(2.0e-3 / est);
         return std::max(4, std::min(64, k));
@@ -1189,60 +1212,77 @@ int Engine::run(hisq_info* infos)
             }
         }
     }
+    static thread_local std::vector<char> tabbuf;
     if (P.size() > 1) {
-        static thread_local std::vector<char> tabbuf;
         tabbuf.resize(std::max(sizeof(BatchTable<double>), sizeof(BatchTable<float>)));
         rc = mixed ? tune_batched<float>(tabbuf.data()) : tune_batched<double>(tabbuf.data());
         if (rc) return rc;
-        if ((rc = setup(host))) return rc;
-        rc = mixed ? upload_table<float>(tabbuf.data(), {}, batch_bs)
-                   : upload_table<double>(tabbuf.data(), {}, batch_bs);
-        if (rc) return rc;
-    } else if ((rc = setup(host))) {
-        return rc;
     }
+    if ((rc = setup(host))) return rc;
 
-    const int kblk = poll_block_size();
     const bool profile = prm.profile != 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    auto release = on_scope_exit([&] {
+    auto drop_graph = [&] {
         if (exec) hipGraphExecDestroy(exec);
         if (graph) hipGraphDestroy(graph);
+        exec = nullptr;
+        graph = nullptr;
+    };
+    auto release = on_scope_exit([&] {
+        drop_graph();
         destroy_events(ev.data(), ev.size());
         ev.clear();
     });
-    if (profile) {
-        ev.assign(4 * kblk, nullptr);
-        for (auto& e : ev) HIP_TRY(hipEventCreate(&e));
-    }
-    // Event timestamps are not available for events recorded inside a graph, so
-    // a profiled solve launches its kernels directly on the stream.
-    // A poll block of more than 16 iterations is one smaller graph launched
-    // several times where that divides it: capturing and instantiating costs
-    // about 4 us per kernel (0.85 ms of a 4.7 ms solve for 64 iterations at
-    // once), and the GPU starts on the first launch while the host issues the rest.
-    // (8^4, one rhs: 2.87 -> 2.75 ms.)
-    int chunk = kblk;
-    if (prm.use_graph && !profile) {
+    int kblk = 0, chunk = 0;
+    // The poll block over the problems that still run: table, size and graph.
+    auto prepare_block = [&](const std::vector<int>& now) -> int {
+        drop_graph();
+        live = now;
+        if (!solo()) {
+            const int r = mixed ? upload_table<float>(tabbuf.data(), live, batch_bs)
+                                : upload_table<double>(tabbuf.data(), live, batch_bs);
+            if (r) return r;
+        }
+        kblk = chunk = poll_block_size();
+        if (profile)
+            while (ev.size() < (size_t)4 * kblk) {
+                hipEvent_t e = nullptr;
+                HIP_TRY(hipEventCreate(&e));
+                ev.push_back(e);
+            }
+        // Event timestamps are not available for events recorded inside a graph,
+        // so a profiled solve launches its kernels directly on the stream.
+        if (!prm.use_graph || profile) return HISQ_OK;
+        // A poll block of more than 16 iterations is one smaller graph launched
+        // several times where that divides it: capturing and instantiating costs
+        // about 4 us per kernel (0.85 ms of a 4.7 ms solve for 64 iterations at
+        // once), and the GPU starts on the first launch while the host issues the rest.
+        // (8^4, one rhs: 2.87 -> 2.75 ms.)
         for (int d = 16; d >= 8 && chunk == kblk && kblk > 16; --d)
             if (kblk % d == 0) chunk = d;
         hipStream_t cap;
-        if ((rc = capture_stream(&cap))) return rc;
+        int r = capture_stream(&cap);
+        if (r) return r;
         HIP_TRY(hipStreamBeginCapture(cap, hipStreamCaptureModeRelaxed));
-        rc = emit_block(cap, chunk, profile);
+        r = emit_block(cap, chunk, false);
         const hipError_t ce = hipStreamEndCapture(cap, &graph);
-        if (rc) return rc;
+        if (r) return r;
         HIP_TRY(ce);
         HIP_TRY(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
-    }
-    auto running = [&]() {
-        for (const Prob& q : P)
-            for (int k = 0; k < q.n; ++k)
-                if (!q.fin[k]) return true;
-        return false;
+        return HISQ_OK;
     };
-    while (running()) {
+    for (;;) {
+        std::vector<int> now;
+        for (size_t j = 0; j < P.size(); ++j)
+            for (int k = 0; k < P[j].n; ++k)
+                if (!P[j].fin[k]) {
+                    now.push_back((int)j);
+                    break;
+                }
+        if (now.empty()) break;
+        // problems of a batch that have ended leave the launches
+        if (now != live && (rc = prepare_block(now))) return rc;
         if (exec) {
             for (int d = 0; d < kblk; d += chunk) HIP_TRY(hipGraphLaunch(exec, s));
         } else if ((rc = emit_block(s, kblk, profile))) {

@@ -83,6 +83,11 @@ __global__ __launch_bounds__(kMaxBlock) void k_pupdate_batched(const BatchTable<
     const CgState* src = bp.state[state_of_phase(phase, 0)];
     CgState* dst = bp.state[state_of_phase(phase, 1)];
     const int fresh = phase == 0;
+    // a problem that has ended within the poll block reads no field (its first
+    // work-group still passes the scalars on)
+    bool any = bid == 0;
+    for (int k = 0; k < bp.n; ++k) any = any || src->active[k] != 0;
+    if (!any) return;
     switch (bp.n) {
     case 1: pupdate_flat<T, 1>(bp.k1, src, dst, fresh, nb, bid); break;
     case 2: pupdate_flat<T, 2>(bp.k1, src, dst, fresh, nb, bid); break;
