@@ -312,12 +312,12 @@ int hisq_trace_estimate(const hisq_geom* g, double mass, int nrhs, const hisq_pa
  * would straddle a time slice) or 3 (XCD j owns z-chunk j of L2/8 planes and
  * walks it x-y position outermost, then t, then z; falls back to 1 unless
  * L2 % 8 == 0 and a tile divides an x-y plane).  stage_rows > 0 selects the
- * LDS-staged Dslash on colour-major fields: a work-group covers stage_rows
- * whole x-rows of one (z, t) plane (block size stage_rows * L0/2 * n /
- * rhs_per_thread, which then replaces block_size) and reads its x and y
- * neighbours from LDS; where that shape is not possible (block not a multiple
- * of 64 or above 512 threads, L1 % stage_rows != 0, staged rows above 64 KB,
- * site-major fields) the unstaged kernel runs.  Neither the order nor the
+ * LDS-staged Dslash: a work-group covers stage_rows whole x-rows of one (z, t)
+ * plane (block size stage_rows * L0/2 * n / rhs_per_thread, rounded up to whole
+ * waves, which then replaces block_size) and reads its x and y neighbours from
+ * LDS; where that shape is not possible (block above 512 threads, and in the
+ * solvers' reducing kernels one that does not fill its waves, L1 % stage_rows
+ * != 0, staged rows above 64 KB) the unstaged kernel runs.  Neither the order nor the
  * staging changes results.  Returns HISQ_EINVAL for an unknown mode or
  * out-of-range values.
  */
@@ -341,8 +341,9 @@ int hisq_set_tuning_eo(int rhs_per_thread, int block_size, int tile_order, int s
  * the workspace of hisq_cg_solve: the same solve, with the same arguments
  * except the workspace, whose scratch (CG scalars, reduction partials and
  * counters, working fields) lives in a static device array of
- * HISQ_NOALLOC_SCRATCH_BYTES per GPU, held from library load to process end.
- * A solve whose hisq_workspace_bytes() exceeds that returns HISQ_EWORKSPACE
+ * HISQ_NOALLOC_SCRATCH_BYTES per GPU (and 512 KiB for reductions), held from
+ * library load to process end.  A solve whose fields and 8 doubles of reduction
+ * scratch per 8 sites exceed that returns HISQ_EWORKSPACE
  * (64 MiB: e.g. 24^3 x 6 with up to 5 rhs in MIXED mode, 32^3 x 8 with one).
  * It calls no hipMalloc, hipFree or other allocating routine: poll blocks run
  * without a hipGraph (params->use_graph and ->profile are ignored) and the

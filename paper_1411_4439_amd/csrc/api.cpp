@@ -326,25 +326,25 @@ int g_force_eo_nr = 0, g_force_eo_bs = 0, g_force_eo_order = 1, g_force_eo_rows 
 bool t_order_ok(const Lat& lat, int n, const Tile& t, int order)
 {
     if (t.split) return order == 0;
-    const int ts = tile_sites(n, t);
+    const int ts = tile_sites(lat, n, t);
     if (order == 2) return lat.Vh / lat.L[3] % ts == 0;
     if (order == 3) return lat.L[2] % 8 == 0 && lat.L[0] * lat.L[1] / 2 % ts == 0;
     return order == 0 || order == 1;
 }
 
 // Block size of the LDS-staged Dslash with R x-rows per tile and G lanes per
-// site, or 0 where that tile is not possible: whole waves, at most
-// kMaxBlockLds threads, tiles that never straddle a plane, staged rows within
-// kMaxStageBytes.
-int staged_block(const Lat& lat, int n, int G, int R, int prec)
+// site, or 0 where that tile is not possible: at most kMaxBlockLds threads,
+// tiles that never straddle a plane, staged rows within kMaxStageBytes; for the
+// reducing kernels whole waves, and lanes that divide one.  (The plain Dslash
+// idles the last lanes of its last wave.)
+int staged_block(const Lat& lat, int n, int G, int R, int prec, int epi)
 {
     if (R < 1) return 0;
-    if (64 % G != 0) return 0;
-    const long bs = (long)R * lat.Lh0 * G;
+    const long used = (long)R * lat.Lh0 * G, bs = (used + 63) / 64 * 64;
     const size_t elt = prec == HISQ_PREC_F64 ? 16 : 8;
     const size_t lds = (size_t)3 * (R + 6) * lat.Lh0 * n * elt;
-    if (bs % 64 != 0 || bs > kMaxBlockLds || lat.L[1] % R != 0 || lds > (size_t)kMaxStageBytes)
-        return 0;
+    if (bs > kMaxBlockLds || lat.L[1] % R != 0 || lds > (size_t)kMaxStageBytes) return 0;
+    if (epi != EPI_PLAIN && (bs != used || 64 % G != 0)) return 0;
     return (int)bs;
 }
 
@@ -373,7 +373,7 @@ Tile split_tile(int n)
 {
     Tile t{1, 64, 0};
     t.split = 1;
-    while (tile_sites(n, t) < kLeastSites) t.bs *= 2;
+    while (tile_sites(Lat{}, n, t) < kLeastSites) t.bs *= 2;
     return t;
 }
 
@@ -403,10 +403,10 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
         frows = eo ? g_force_eo_rows : g_force_rows;
     }
     // a reducing kernel's work-group covers at least kLeastSites sites
-    auto enough = [&](const Tile& c) { return epi == EPI_PLAIN || tile_sites(n, c) >= kLeastSites; };
+    auto enough = [&](const Tile& c) { return epi == EPI_PLAIN || tile_sites(lat, n, c) >= kLeastSites; };
     if (mode == 1 && valid_nr(n, fnr)) {
-        int sbs = cm ? staged_block(lat, n, n / fnr, frows, prec) : 0;
-        if (sbs && !enough(Tile{fnr, sbs, 0})) sbs = 0;
+        int sbs = staged_block(lat, n, n / fnr, frows, prec, epi);
+        if (sbs && !enough(Tile{fnr, sbs, 0, frows})) sbs = 0;
         while (!enough(Tile{fnr, fbs, 0})) fbs *= 2;
         Tile t{fnr, sbs ? sbs : fbs, ford, sbs ? frows : 0};
         if (!t_order_ok(lat, n, t, t.remap)) t.remap = 1;
@@ -434,18 +434,17 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
     hipEvent_t e0 = tev[0], e1 = tev[1];
     Tile best = default_tile(n, prec);
     float best_ms = 1e30f;
-    // candidates: unstaged tiles of 64, 128, 256 threads, then (colour-major
-    // only) LDS-staged tiles of 1..16 rows
+    // candidates: unstaged tiles of 64, 128, 256 threads, then LDS-staged tiles
+    // of 1..16 rows
     std::vector<Tile> cand;
     for (int G = 1; G <= n; ++G) {
         if (n % G != 0) continue;
         for (int bs : {64, 128, 256})
             if (enough(Tile{n / G, bs, 0})) cand.push_back(Tile{n / G, bs, 0, 0});
-        if (cm)
-            for (int R = 1; R <= 16; ++R) {
-                const int sbs = staged_block(lat, n, G, R, prec);
-                if (sbs && enough(Tile{n / G, sbs, 0})) cand.push_back(Tile{n / G, sbs, 0, R});
-            }
+        for (int R = 1; R <= 16; ++R) {
+            const int sbs = staged_block(lat, n, G, R, prec, epi);
+            if (sbs && enough(Tile{n / G, sbs, 0, R})) cand.push_back(Tile{n / G, sbs, 0, R});
+        }
     }
     if (cm && (epi == EPI_NORM || epi == EPI_CG) && small_launch(lat, n, 4)) {
         Tile c = split_tile(n);
@@ -1519,10 +1518,17 @@ int hisq::report_error(int code, const char* fmt, ...)
     return code;
 }
 
-size_t hisq::cg_workspace_bytes(const Lat& lat, int nrhs, int mode)
+size_t hisq::no_alloc_bytes(const hisq_geom* g, int nrhs, int mode)
 {
-    Ws w;
-    return ws_layout(lat, nrhs, mode, WS_SOLVE, nullptr, &w);
+    const size_t ws = hisq_workspace_bytes(g, nrhs, mode);
+    if (ws == 0) return 0;
+    const Lat lat = make_lat(*g);
+    const size_t used = align256(2 * sizeof(CgState)) + align256(red_doubles(lat.Vh, nrhs) * sizeof(double)) +
+                        align256(kRedCounters * sizeof(uint32_t));
+    const size_t blocks = (size_t)lat.Vh / 8 + 1, groups = (blocks + 63) / 64;
+    const size_t counted = align256((blocks + groups) * HISQ_MAX_RHS * sizeof(double)) +
+                           align256((1 + groups) * sizeof(uint32_t));
+    return ws - used + counted;
 }
 
 // ===========================================================================

@@ -275,13 +275,14 @@ __device__ __forceinline__ void dslash_site_split(const Lat& lat, int P, int i, 
 }
 
 // ---------------------------------------------------------------------------
-// LDS-staged form (colour-major fields).  A work-group covers R whole x-rows
+// LDS-staged form.  A work-group covers R whole x-rows
 // of one (z, t) plane.  The input rows y0-3 .. y0+R+2 of that plane (periodic
-// in y) are copied to LDS once, laid out [3][R+6][L0/2][n]; the x and y
+// in y) are copied to LDS once, laid out [3][R+6][L0/2][n] (colour-major fields)
+// or [R+6][L0/2][3][n] (site-major ones, plain Dslash only); the x and y
 // neighbours (8 of the 16 slots) are then read from LDS and only the z and t
 // neighbours and the links come from global memory.
 
-template <typename T, int NRHS>
+template <typename T, int NRHS, bool CM>
 __device__ __forceinline__ void stage_rows(const cplx<T>* __restrict__ in, cplx<T>* lds,
                                            const Lat& lat, int row0, int R)
 {
@@ -318,6 +319,40 @@ __device__ __forceinline__ void stage_rows(const cplx<T>* __restrict__ in, cplx<
         c = (cj >= rows ? 1u : 0u) + (cj >= 2 * rows ? 1u : 0u);
         j = cj - c * rows;
     };
+    if constexpr (!CM) {
+        // a row is one contiguous stretch of all three colours, in LDS as in memory
+        constexpr unsigned elt = sizeof(cplx<T>);
+        if (elt == 16 || (lat.Lh0 * 3 * NRHS) % 2 == 0) {
+            const unsigned chunk = (unsigned)(lat.Lh0 * 3 * NRHS) * elt / 16;
+            const unsigned total = rows * chunk;
+            const float inv = 1.0f / (float)chunk;
+            const f4* src = reinterpret_cast<const f4*>(in);
+            f4* dst = reinterpret_cast<f4*>(lds);
+            for (unsigned u0 = threadIdx.x; u0 < total; u0 += kStageBatch * nt) {
+                f4 buf[kStageBatch];
+#pragma unroll
+                for (unsigned q = 0; q < kStageBatch; ++q) {
+                    const unsigned u = u0 + q * nt;
+                    if (u < total) {
+                        unsigned c, j, off;
+                        split(u, chunk, inv, c, j, off);
+                        j += c * rows;
+                        buf[q] = src[row_site(j) * (3 * NRHS) * elt / 16 + off];
+                    }
+                }
+#pragma unroll
+                for (unsigned q = 0; q < kStageBatch; ++q)
+                    if (u0 + q * nt < total) dst[u0 + q * nt] = buf[q];
+            }
+        } else {
+            const unsigned chunk = (unsigned)(lat.Lh0 * 3 * NRHS);
+            for (unsigned u = threadIdx.x; u < rows * chunk; u += nt) {
+                const unsigned j = u / chunk;
+                lds[u] = in[row_site(j) * (3 * NRHS) + (u - j * chunk)];
+            }
+        }
+        return;
+    }
     if constexpr (sizeof(T) == 4) {
         if ((lat.Lh0 * NRHS) % 2 == 0) {
             // 16-byte units of two complex numbers
@@ -364,11 +399,11 @@ __device__ __forceinline__ void stage_rows(const cplx<T>* __restrict__ in, cplx<
     }
 }
 
-template <typename T, int NRHS, int NR>
+template <typename T, int NRHS, int NR, bool CM>
 __device__ __forceinline__ void load_vec_lds(const cplx<T>* lds, int cstride, int site, int g,
                                              cplx<T> (&v)[3][NR])
 {
-    const cplx<T>* vp = lds + site * NRHS + g * NR;
+    const cplx<T>* vp = lds + site * (CM ? NRHS : 3 * NRHS) + g * NR;
 #pragma unroll
     for (int b = 0; b < 3; ++b) load_rhs<NR>(vp + b * cstride, v[b]);
 }
@@ -404,7 +439,7 @@ struct LdsHead {
     cplx<T> v0[3][NR], v1[3][NR];
 };
 
-template <typename T, int NRHS, int NR, int NK>
+template <typename T, int NRHS, int NR, int NK, bool CM>
 __device__ __forceinline__ void lds_head(const Lat& lat, int P, int i, int g,
                                          const cplx<T>* __restrict__ lk,
                                          const cplx<T>* __restrict__ in, LdsHead<T, NRHS, NR, NK>& h)
@@ -412,11 +447,11 @@ __device__ __forceinline__ void lds_head(const Lat& lat, int P, int i, int g,
     const SiteCoord sc = site_coord(lat, P, i);
     constexpr int G = link_group<NRHS, NR>();
     load_link_part<T, NK, slot_at(0), G>(lk, lat.Vh, i, g % G, h.m);
-    load_vec<T, NRHS, NR, true>(in, lat.Vh, neighbour<slot_at(0)>(lat, sc), g, h.v0);
-    load_vec<T, NRHS, NR, true>(in, lat.Vh, neighbour<slot_at(2)>(lat, sc), g, h.v1);
+    load_vec<T, NRHS, NR, CM>(in, lat.Vh, neighbour<slot_at(0)>(lat, sc), g, h.v0);
+    load_vec<T, NRHS, NR, CM>(in, lat.Vh, neighbour<slot_at(2)>(lat, sc), g, h.v1);
 }
 
-template <typename T, int NRHS, int NR, int NK, bool PN>
+template <typename T, int NRHS, int NR, int NK, bool CM, bool PN>
 __device__ __forceinline__ void dslash_site_lds(const Lat& lat, int P, int i, int g, int r,
                                                 const cplx<T>* __restrict__ lk,
                                                 const cplx<T>* __restrict__ in,
@@ -428,7 +463,7 @@ __device__ __forceinline__ void dslash_site_lds(const Lat& lat, int P, int i, in
     const int Vh = lat.Vh;
     const SiteCoord sc = site_coord(lat, P, i);
     const int xh = i - sc.row;
-    const int cstride = rows * lat.Lh0 * NRHS;
+    const int cstride = CM ? rows * lat.Lh0 * NRHS : NRHS;
 #pragma unroll
     for (int c = 0; c < 3; ++c)
 #pragma unroll
@@ -457,10 +492,10 @@ __device__ __forceinline__ void dslash_site_lds(const Lat& lat, int P, int i, in
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (k + 2 < 16) load_link_part<T, NK, slot_at(k + 2), G>(lk, Vh, i, gl, m[k & 1]);
             if constexpr (k + 4 < 16)
-                load_vec<T, NRHS, NR, true>(in, Vh, neighbour<slot_at(k + 4)>(lat, sc), g,
-                                            vg[(k >> 1) & 1]);
-            load_vec_lds<T, NRHS, NR>(lds, cstride,
-                                      lds_neighbour<slot_at(k + 1)>(lat, r, xh, sc.x), g, vl);
+                load_vec<T, NRHS, NR, CM>(in, Vh, neighbour<slot_at(k + 4)>(lat, sc), g,
+                                          vg[(k >> 1) & 1]);
+            load_vec_lds<T, NRHS, NR, CM>(lds, cstride,
+                                          lds_neighbour<slot_at(k + 1)>(lat, r, xh, sc.x), g, vl);
         } else {
             C mk[9];
             share_link<T, NK, slot_at(k), G>(m[k & 1], mk);
@@ -469,7 +504,7 @@ __device__ __forceinline__ void dslash_site_lds(const Lat& lat, int P, int i, in
         __builtin_amdgcn_sched_barrier(0);
     });
     if constexpr (PN) {
-        load_vec_lds<T, NRHS, NR>(lds, cstride, (r + 3) * lat.Lh0 + xh, g, vl);
+        load_vec_lds<T, NRHS, NR, CM>(lds, cstride, (r + 3) * lat.Lh0 + xh, g, vl);
         own_norm<T, NR>(vl, own);
     }
 }
@@ -503,7 +538,9 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
         for (int k = 0; k < NRHS; ++k) any_prob = any_prob || (state->active[k] != 0);
         if (!any_prob) return;
     }
-    const int g = Map::group();
+    // a staged tile's lanes run on from site to site, across waves; where they
+    // do not fill the last wave (plain Dslash only), its last lanes idle
+    const int g = ST ? (int)threadIdx.x % G : Map::group();
     const int mu = Map::dir();  // split form: this lane's direction, then its colour
     constexpr int M = EPI == EPI_NORM ? 2 : 1;  // |p|^2 and |t|^2, or one sum
     double part[M][NR];
@@ -526,20 +563,21 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
     T ns = T(1);  // r9: the Naik scale of the links
     if constexpr (NK == HISQ_NAIK_R9) ns = (T)*a.naik_scale;
 
-    const int i = Map::site(tile);
+    const int stage_sites = ST ? a.rows * a.lat.Lh0 : 0;
+    const int i = ST ? tile * stage_sites + (int)threadIdx.x / G : Map::site(tile);
+    const bool live = ST ? (int)threadIdx.x < stage_sites * G : Map::live();
     LdsHead<T, NRHS, NR, NK> head;
     if constexpr (ST) {
         // the tile is `rows` whole x-rows: stage them and their +-3 row halo
-        static_assert(CM, "staging reads colour-major fields");
-        if (i < a.lat.Vh) lds_head<T, NRHS, NR, NK>(a.lat, a.parity, i, g, a.links, a.in, head);
-        stage_rows<T, NRHS>(a.in, lds, a.lat, tile * a.rows, a.rows);
+        if (live) lds_head<T, NRHS, NR, NK, CM>(a.lat, a.parity, i, g, a.links, a.in, head);
+        stage_rows<T, NRHS, CM>(a.in, lds, a.lat, tile * a.rows, a.rows);
         __syncthreads();
     }
     // The epilogue computes everything before its stores, posts the
     // work-group's reduction partials, and only then stores the outputs: the
     // completion wait that orders the partials before the counter update does
     // not wait for the output stores.
-    bool on_site = Map::live() && i < a.lat.Vh;
+    bool on_site = live && i < a.lat.Vh;
     using Lay = Layout<NRHS, CM>;
     const int base = Lay::site(on_site ? i : 0) + g * NR;
     constexpr int NC = SPL == 1 ? 3 : 1;  // colours this lane stores
@@ -560,7 +598,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
 #pragma unroll
             for (int k = 0; k < NR; ++k) acc[0][k] = mu == 0 ? acc[0][k] : mu == 1 ? acc[1][k] : acc[2][k];
         } else if constexpr (ST)
-            dslash_site_lds<T, NRHS, NR, NK, EPI == EPI_NORM>(
+            dslash_site_lds<T, NRHS, NR, NK, CM, EPI == EPI_NORM>(
                 a.lat, a.parity, i, g, ((int)threadIdx.x / G) / a.lat.Lh0, a.links, a.in, lds,
                 a.rows + 6, head, acc, ns, part[0]);
         else
@@ -582,11 +620,11 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
         const bool frozen = state->frozen != 0;
         const T al = on && good && !frozen ? (T)(state->rr[kl] / den) : T(0);
         if (bid == 0 && threadIdx.x < NRHS && on && !good && !frozen) state->brk[kl] = 1;
-        const int live = on && (good || frozen);
+        const int runs = on && (good || frozen);
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
             alpha[k] = __shfl(al, g * NR + k, 64);
-            act[k] = __shfl(live, g * NR + k, 64) != 0;
+            act[k] = __shfl(runs, g * NR + k, 64) != 0;
             any_act = any_act || act[k];
         }
     }
@@ -600,7 +638,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
             if (any_act) {
             // converged (masked) rhs are not written (and not read where the
             // whole tile of the thread is masked); their partial sums stay
-            // zero and their finisher ignores them
+            // zero and are ignored
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 C pv[NR];
@@ -685,13 +723,13 @@ __global__ __launch_bounds__(kMaxBlock) HISQ_KATTR void k_dslash(const DslashArg
         a, a.state, tile_of_block(blockIdx.x, gridDim.x, a.remap, a.lat, tile_sites), gridDim.x, blockIdx.x);
 }
 
-template <typename T, int NRHS, int NR, int NK, int EPI>
+template <typename T, int NRHS, int NR, int NK, int EPI, bool CM>
 __global__ __launch_bounds__(kMaxBlockLds) void k_dslash_lds(const DslashArgs<T> a)
 {
     extern __shared__ __align__(16) unsigned char hisq_stage[];
-    const int tile_sites = (int)blockDim.x / (NRHS / NR);
-    dslash_tile<T, NRHS, NR, NK, EPI, true, true>(
-        a, a.state, tile_of_block(blockIdx.x, gridDim.x, a.remap, a.lat, tile_sites), gridDim.x, blockIdx.x,
+    const int sites = a.rows * a.lat.Lh0;
+    dslash_tile<T, NRHS, NR, NK, EPI, CM, true>(
+        a, a.state, tile_of_block(blockIdx.x, gridDim.x, a.remap, a.lat, sites), gridDim.x, blockIdx.x,
         reinterpret_cast<cplx<T>*>(hisq_stage));
 }
 
@@ -751,12 +789,21 @@ static hipError_t go(const Tile& t, DslashArgs<T> a, hipStream_t s, bool cm)
         }
     }
     if (t.rows > 0) {
-        // LDS-staged: colour-major only; the host has checked that a tile is
-        // t.rows whole x-rows of one plane and that the rows fit in LDS
-        if (!cm) return hipErrorInvalidValue;
+        // LDS-staged: the host has checked that a tile is t.rows whole x-rows of
+        // one plane and that the rows fit in LDS.  The reducing kernels need the
+        // tile to fill its waves, and a site's lanes to divide one.
         const size_t lds = (size_t)3 * (t.rows + 6) * a.lat.Lh0 * NRHS * sizeof(cplx<T>);
-        if constexpr (64 % (NRHS / NR) == 0) {
-            hipLaunchKernelGGL((k_dslash_lds<T, NRHS, NR, NK, EPI>), dim3(a.ntiles), dim3(t.bs), lds, s, a);
+        const int used = t.rows * a.lat.Lh0 * (NRHS / NR);
+        if (used > t.bs || t.bs - used >= 64) return hipErrorInvalidValue;
+        if constexpr (EPI == EPI_PLAIN) {
+            if (cm)
+                hipLaunchKernelGGL((k_dslash_lds<T, NRHS, NR, NK, EPI, true>), dim3(a.ntiles), dim3(t.bs), lds, s, a);
+            else
+                hipLaunchKernelGGL((k_dslash_lds<T, NRHS, NR, NK, EPI, false>), dim3(a.ntiles), dim3(t.bs), lds, s, a);
+            return hipGetLastError();
+        } else if constexpr (64 % (NRHS / NR) == 0) {
+            if (!cm || used != t.bs) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((k_dslash_lds<T, NRHS, NR, NK, EPI, true>), dim3(a.ntiles), dim3(t.bs), lds, s, a);
             return hipGetLastError();
         } else {
             return hipErrorInvalidValue;

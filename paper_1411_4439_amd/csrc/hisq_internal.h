@@ -270,10 +270,13 @@ struct Tile {
 
 // Sites per work-group and work-groups of a Dslash launch of n rhs: a wave holds
 // as many whole sites as its 64 lanes allow.
-inline int tile_sites(int n, const Tile& t) { return t.bs / 64 * (64 / (n / t.nr * (t.split ? 4 : 1))); }
+inline int tile_sites(const Lat& lat, int n, const Tile& t)
+{
+    return t.rows > 0 ? t.rows * lat.Lh0 : t.bs / 64 * (64 / (n / t.nr * (t.split ? 4 : 1)));
+}
 inline int tile_blocks(const Lat& lat, int n, const Tile& t)
 {
-    const int ts = tile_sites(n, t);
+    const int ts = tile_sites(lat, n, t);
     return (lat.Vh + ts - 1) / ts;
 }
 
@@ -363,7 +366,10 @@ hipError_t launch_redot(const d2* y, const d2* x, int Vh, int nrhs, double scale
 int cg_solve_on(const hisq_geom* g, double mass, int nrhs, const hisq_params* p,
                 const void* links64, const void* links32, const double* b_e, double* x_e,
                 void* ws, size_t ws_bytes, hisq_info* info, void* stream, CgState* host_buf);
-size_t cg_workspace_bytes(const Lat& lat, int nrhs, int mode);
+// The size that the limit of hisq_cg_solve_noalloc is counted in: the solve's
+// fields with 8 doubles of reduction scratch per 8 sites, whatever scratch the
+// kernels use (0 on invalid input).
+size_t no_alloc_bytes(const hisq_geom* g, int nrhs, int mode);
 // Sets the message of hisq_last_error() for this thread; returns code.
 int report_error(int code, const char* fmt, ...);
 

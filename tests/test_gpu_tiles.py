@@ -74,3 +74,28 @@ def test_forced_one_rhs_per_lane_solve():
         x, st, info = H.solve(links, m, dev(b), mode=mode, naik=nk)
         assert st == H.HISQ_OK and info["rhs_per_thread"] == 1
         assert oracle.residual(L, U, N, m, b, host(x)).max() <= 1e-10
+
+
+@pytest.mark.parametrize("L", [(6, 4, 6, 4), (12, 12, 4, 4), (10, 8, 8, 4)])
+@pytest.mark.parametrize("n", [1, 3, 5, 8])
+def test_staged_rows_in_both_field_orders(L, n):
+    """Staged x-rows on site-major fields, and tiles whose last wave is not full
+    (L0/2 * lanes * rows no multiple of 64), give the bits of the unstaged tile of
+    the same rhs per lane."""
+    H = gpu_lib()
+    U, N = W.make_links(L, 0.3, 841)
+    links = H.Links(L, dev(U), dev(N))
+    v = W.make_sources(L, n, 842)
+    want = oracle.dslash_eo(L, U, N, v, 0)
+    for prec, nk, tol in ((H.PREC_F64, H.NAIK_FULL, 1e-13), (H.PREC_F32, H.NAIK_R14, 1e-6)):
+        for layout in (H.LAYOUT_SITE, H.LAYOUT_COLOUR):
+            f = dev(v if layout == H.LAYOUT_SITE else np.ascontiguousarray(v.transpose(1, 0, 2)))
+            f = f if prec == H.PREC_F64 else f.to(dev(v[:1].astype(np.complex64)).dtype)
+            for nr in {n, 1}:
+                H.hisq_set_tuning(1, nr, 64, 0, 0)
+                plain = host(H.dslash(links, 0, f, prec, nk, layout=layout))
+                g = plain if layout == H.LAYOUT_SITE else plain.transpose(1, 0, 2)
+                assert rel_l2_per_rhs(g.astype(np.complex128), want) <= tol
+                for rows, order in ((1, 0), (2, 1), (4, 2), (4, 3)):
+                    H.hisq_set_tuning(1, nr, 64, order, rows)
+                    assert np.array_equal(host(H.dslash(links, 0, f, prec, nk, layout=layout)), plain), (nr, rows)
