@@ -563,7 +563,7 @@ __device__ __forceinline__ void dslash_tile(const DslashArgs<T>& a, CgState* sta
     // (D_eo^dag = -D_oe); a rhs whose <p, A p> is not positive and finite is
     // masked here and reported.  The first wave works it out, before its sites,
     // and leaves it in LDS (in every wave it was 15% more load instructions:
-    // 331 us instead of 326 at 48^3 x 12, 8 rhs, 256 threads).
+    // 331 us instead of 324 at 48^3 x 12, 8 rhs, 256 threads).
     __shared__ T cg_alpha[EPI == EPI_CG ? kMaxRhs : 1];
     __shared__ int cg_live[EPI == EPI_CG ? kMaxRhs : 1];
     if constexpr (EPI == EPI_CG) {
