@@ -450,24 +450,45 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
         Tile c = split_tile(n);
         for (; c.bs <= kMaxBlock; c.bs *= 2) cand.push_back(c);
     }
+    auto timed = [&](const Tile& c, int reps, float* ms) -> int {
+        HIP_TRY(hipEventRecord(e0, s));
+        for (int rep = 0; rep < reps; ++rep) HIP_TRY(launch_ds(epi, n, nk, c, probe, s, cm));
+        HIP_TRY(hipEventRecord(e1, s));
+        HIP_TRY(hipEventSynchronize(e1));
+        HIP_TRY(hipEventElapsedTime(ms, e0, e1));
+        return HISQ_OK;
+    };
+    std::vector<std::pair<float, Tile>> tried;
     for (const Tile& base : cand) {
         for (int remap = 0; remap < 4; ++remap) {
-                Tile c = base;
-                c.remap = remap;
-                if (!t_order_ok(lat, n, c, remap)) continue;
-                if (launch_ds(epi, n, nk, c, probe, s, cm) != hipSuccess) continue;
-                HIP_TRY(hipEventRecord(e0, s));
-                for (int rep = 0; rep < 3; ++rep) HIP_TRY(launch_ds(epi, n, nk, c, probe, s, cm));
-                HIP_TRY(hipEventRecord(e1, s));
-                HIP_TRY(hipEventSynchronize(e1));
-                float ms = 0;
-                HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-                if (ms < best_ms) {
-                    best_ms = ms;
-                    best = c;
-                }
-            }
+            Tile c = base;
+            c.remap = remap;
+            if (!t_order_ok(lat, n, c, remap)) continue;
+            if (launch_ds(epi, n, nk, c, probe, s, cm) != hipSuccess) continue;
+            float ms = 0;
+            const int rc = timed(c, 3, &ms);
+            if (rc) return rc;
+            tried.emplace_back(ms, c);
+        }
     }
+    // Three launches order the candidates to a few percent; the first four run
+    // again in turn, so that the choice is not the luckiest of a hundred.
+    std::sort(tried.begin(), tried.end(),
+              [](const std::pair<float, Tile>& x, const std::pair<float, Tile>& y) { return x.first < y.first; });
+    if (tried.size() > 4) tried.resize(4);
+    for (auto& t : tried) t.first = 0;
+    for (int round = 0; round < 3; ++round)
+        for (auto& t : tried) {
+            float ms = 0;
+            const int rc = timed(t.second, 6, &ms);
+            if (rc) return rc;
+            t.first += ms;
+        }
+    for (const auto& t : tried)
+        if (t.first < best_ms) {
+            best_ms = t.first;
+            best = t.second;
+        }
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         g_tune_cache[key] = best;
