@@ -131,25 +131,23 @@ __device__ __forceinline__ void store_slot(T* slot, int Vh, int i, const double 
 }
 
 // Largest (smallest) of non-negative floats over the wave, by their bits, into a
-// header word.  Waves whose value is no larger than what they find there
-// issue no atomic: atomics on one address are served one after another.
-__device__ __forceinline__ void header_max(uint32_t* word, float v)
+// header word.  As integers, not as floats: fmaxf and fminf drop a NaN, the bits of
+// one exceed every finite float's, so that a NaN scale (a NaN link) reaches the
+// header and the host refuses the field.  Waves whose value is no larger than what
+// they find there issue no atomic: atomics on one address are served one after another.
+__device__ __forceinline__ void header_max(uint32_t* word, uint32_t bits)
 {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    if ((threadIdx.x & 63) == 0) {
-        const uint32_t bits = __float_as_uint(v);
-        if (bits > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(word, bits);
-    }
+    for (int off = 32; off >= 1; off >>= 1) bits = max(bits, (uint32_t)__shfl_xor((int)bits, off, 64));
+    if ((threadIdx.x & 63) == 0 && bits > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(word, bits);
 }
-__device__ __forceinline__ void header_min(uint32_t* word, float v)
+__device__ __forceinline__ void header_min(uint32_t* word, uint32_t bits)
 {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fminf(v, __shfl_xor(v, off, 64));
-    if ((threadIdx.x & 63) == 0) {
-        const uint32_t bits = __float_as_uint(v);
-        if (bits < __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(word, bits);
-    }
+    for (int off = 32; off >= 1; off >>= 1) bits = min(bits, (uint32_t)__shfl_xor((int)bits, off, 64));
+    if ((threadIdx.x & 63) == 0 && bits < __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMin(word, bits);
 }
 
 // One thread per link: it reads the link once and writes both of its uses, the
@@ -166,7 +164,7 @@ constexpr int kPackSites = 256;
 
 template <typename T, int NK, bool NAIK>
 __device__ __forceinline__ void pack_link(const Lat& lat, const d2 (&m)[9], int mu, const int (&c)[4],
-                                          T* __restrict__ out, bool on, float& worst, float& smin, float& smax)
+                                          T* __restrict__ out, bool on, uint32_t& worst, uint32_t& smin, uint32_t& smax)
 {
     constexpr int NR = NAIK ? naik_reals(NK) : 18;
     constexpr int h = NAIK ? 3 : 1;
@@ -176,9 +174,9 @@ __device__ __forceinline__ void pack_link(const Lat& lat, const d2 (&m)[9], int 
 #pragma unroll
     for (int nu = 0; nu < 4; ++nu)
         if (nu == mu) y[nu] = (c[nu] + h) % lat.L[nu];
-    worst = 0.0f;
-    smin = 3.0e38f;
-    smax = 0.0f;
+    worst = 0u;
+    smin = 0x7f800000u;  // +inf
+    smax = 0u;
     if (!on) return;
 #pragma unroll
     for (int back = 0; back < 2; ++back) {
@@ -195,9 +193,9 @@ __device__ __forceinline__ void pack_link(const Lat& lat, const d2 (&m)[9], int 
         const int slot = (NAIK ? 8 : 0) + 4 * back + mu;
         store_slot<T, NR>(blk + (size_t)slot_real_start(slot, NK) * Vh, Vh,
                           site_of(lat, back ? y : c) >> 1, re);
-        worst = fmaxf(worst, err);
-        smin = fminf(smin, sc);
-        smax = fmaxf(smax, sc);
+        worst = max(worst, __float_as_uint(err));
+        smin = min(smin, __float_as_uint(sc));
+        smax = max(smax, __float_as_uint(sc));
     }
 }
 
@@ -226,7 +224,7 @@ __global__ __launch_bounds__(kPackSites) void k_pack(Lat lat, const d2* __restri
     d2 m[9];
 #pragma unroll
     for (int e = 0; e < 9; ++e) m[e] = sm[(s - s0) * 9 + e];
-    float worst, smin, smax;
+    uint32_t worst, smin, smax;
     if (!naik) {
         pack_link<T, NK, false>(lat, m, mu, c, out, on, worst, smin, smax);
     } else {
