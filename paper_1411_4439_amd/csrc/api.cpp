@@ -348,7 +348,27 @@ int staged_block(const Lat& lat, int n, int G, int R, int prec, int epi)
     return (int)bs;
 }
 
-Tile default_tile(int n, int prec)
+// FP64 bundles of 5 and 7 rhs on the built-in tile: one rhs per lane, or the bundle?
+// One per lane makes 5 or 7 times as many waves, but every lane repeats the link
+// loads of its site: it pays where the bundle per lane leaves the chip short of waves.
+// Plain Dslash, up to 16384 half-sites (256 waves, one per CU); us, one / n per lane,
+// n = 5 and 7: 16^3 x 8 16.3 / 18.4, 20.4 / 23.5; 20^3 x 6 (24000) 20.9 / 20.0,
+// 29.3 / 24.9; 32^3 x 8 104 / 91.5, 137 / 116; 48^3 x 12 514 / 442, 688 / 564.
+// Reducing kernels (fewer waves fit beside each other), where the work-groups of the
+// bundle per lane (128 sites, 256 CUs) leave their first or second round less than
+// 4/5 full, and in the third; ms of 60 iterations: 20^3 x 6 (188 work-groups) 4.1 / 4.3,
+// 5.3 / 5.5; 20^3 x 8 (250) 5.6 / 4.8, 6.5 / 6.2; 24^3 x 6 (324) 6.4 / 6.8, 7.9 / 8.8;
+// 24^3 x 8 (432) 8.0 / 7.3, 9.8 / 9.8; 28^3 x 8 (686) 11.5 / 12.7, 15.0 / 17.7;
+// 32^3 x 6 (768) 12.6 / 13.0, 16.2 / 18.0; 32^3 x 8 (1024) 16.5 / 15.4, 22.0 / 21.8;
+// 48^3 x 12 83 / 77, 117 / 112.
+bool one_rhs_per_lane(const Lat& lat, int epi)
+{
+    if (epi == EPI_PLAIN) return lat.Vh <= 16384;
+    const int wgs = (lat.Vh + 127) / 128, rounds = (wgs + 255) / 256;
+    return rounds == 3 || (rounds < 3 && 5 * wgs < 4 * 256 * rounds);
+}
+
+Tile default_tile(const Lat& lat, int n, int prec, int epi = EPI_PLAIN)
 {
     Tile t{n, 128, 1};
     if (prec == HISQ_PREC_F64 && n > 4) {
@@ -357,6 +377,7 @@ Tile default_tile(int n, int prec)
                 t.nr = nr;
                 break;
             }
+        if (t.nr == 1 && !one_rhs_per_lane(lat, epi)) t.nr = n;
     }
     return t;
 }
@@ -414,7 +435,7 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
         return HISQ_OK;
     }
     if (mode != 0) {
-        *out = default_tile(n, prec);
+        *out = default_tile(lat, n, prec, epi);
         if (cm && (epi == EPI_NORM || epi == EPI_CG) && small_launch(lat, n, 1)) *out = split_tile(n);
         return HISQ_OK;
     }
@@ -432,7 +453,7 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
     HIP_TRY(hipEventCreate(&tev[0]));
     HIP_TRY(hipEventCreate(&tev[1]));
     hipEvent_t e0 = tev[0], e1 = tev[1];
-    Tile best = default_tile(n, prec);
+    Tile best = default_tile(lat, n, prec, epi);
     float best_ms = 1e30f;
     // candidates: unstaged tiles of 64, 128, 256 threads, then LDS-staged tiles
     // of 1..16 rows
@@ -1369,7 +1390,7 @@ int full_impl(double mass, int n, const hisq_params* p, const void* links64, con
               hipStream_t s, const Lat& lat)
 {
     const size_t nc = (size_t)lat.Vh * 3 * n;
-    const Tile t = default_tile(n, HISQ_PREC_F64);
+    const Tile t = default_tile(lat, n, HISQ_PREC_F64);
     DslashArgs<double> a{};
     a.lat = lat;
     a.parity = 0;
@@ -1404,7 +1425,7 @@ int apply_dM(double mass, int n, int nder, const void* links64, const d2* x_e, c
                                   y_o, s));
         return HISQ_OK;
     }
-    const Tile t = default_tile(n, HISQ_PREC_F64);
+    const Tile t = default_tile(lat, n, HISQ_PREC_F64);
     DslashArgs<double> a{};
     a.lat = lat;
     for (int par = 0; par < 2; ++par) {
@@ -1767,7 +1788,7 @@ int hisq_cg_solve_backward(const hisq_geom* g, double mass, int nrhs, const hisq
     const d2* yc = w.xc;
     d2* xc = w.r64;
     HIP_TRY(launch_layout(reinterpret_cast<const d2*>(x_e), xc, lat.Vh, nrhs, true, s));
-    Tile t = default_tile(nrhs, HISQ_PREC_F64);
+    Tile t = default_tile(lat, nrhs, HISQ_PREC_F64);
     DslashArgs<double> a{};
     a.lat = lat;
     a.parity = 1;
@@ -1831,7 +1852,7 @@ int hisq_dslash_dmu(const hisq_geom* g, int out_parity, int nrhs, int nder, cons
     a.links = lk;
     a.in = vin;
     a.out = vout;
-    HIP_TRY(launch_ds(EPI_PLAIN, nrhs, HISQ_NAIK_FULL, default_tile(nrhs, HISQ_PREC_F64), a, s, false));
+    HIP_TRY(launch_ds(EPI_PLAIN, nrhs, HISQ_NAIK_FULL, default_tile(lat, nrhs, HISQ_PREC_F64), a, s, false));
     return HISQ_OK;
 }
 
