@@ -1,0 +1,52 @@
+"""What the autotuner costs the first call of a shape, and that its choice is good."""
+import time
+
+import numpy as np
+import pytest
+
+from paper_1411_4439_amd import workload as W
+from tests.gpu_util import dev, gpu_lib
+
+pytestmark = pytest.mark.gpu
+
+L = (32, 32, 24, 12)  # a shape that no other test has tuned
+
+
+@pytest.mark.parametrize("prec,n", [("f64", 5), ("f64", 8), ("r14", 7)])
+def test_first_call_of_a_shape(prec, n):
+    """The tuner may take the time of 150 later calls, and 8 ms for loading kernels (it
+    takes about 60 and 3); every tile in every order took 250 to 550.  Its choice is no
+    slower than the built-in tile."""
+    import torch
+    H = gpu_lib()
+    U, N = W.make_links((32, 4, 4, 12), 0.3, 871)  # the links' values do not matter: tiled over the lattice
+    def tile(a):
+        a = a.reshape((4, 12, 4, 4, 32, 3, 3))
+        return np.tile(a, (1, 1, 6, 8, 1, 1, 1)).reshape((4, 32 * 32 * 24 * 12, 3, 3))
+    links = H.Links(L, dev(tile(U)), dev(tile(N)), f32=False, r14=prec == "r14")
+    args = (H.PREC_F64, H.NAIK_FULL) if prec == "f64" else (H.PREC_F32, H.NAIK_R14)
+    v = torch.randn(32 * 32 * 24 * 12 // 2, 3, n, dtype=torch.complex128 if prec == "f64" else torch.complex64,
+                    device="cuda")
+    out = torch.empty_like(v)
+
+    def call(times):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(times):
+            H.hisq_dslash(L, 1, n, *args, H.LAYOUT_SITE, links.packed(*args), v, out)
+        torch.cuda.synchronize()
+        return (time.perf_counter() - t) / times
+
+    try:
+        H.hisq_set_tuning(2)
+        call(20)
+        builtin = min(call(50) for _ in range(5))
+        H.hisq_set_tuning(0)
+        first = call(1)
+        later = min(call(50) for _ in range(5))
+    finally:
+        H.hisq_set_tuning(0)
+    print(prec, n, "first %.2f ms, later %.1f us, built-in tile %.1f us" % (first * 1e3, later * 1e6, builtin * 1e6),
+          flush=True)
+    assert first <= 150 * later + 8e-3
+    assert later <= 1.03 * builtin
