@@ -305,9 +305,7 @@ int hisq_trace_estimate(const hisq_geom* g, double mass, int nrhs, const hisq_pa
  * stage_rows;
  * mode 2: built-in default, no timing.  rhs_per_thread must divide the bundle
  * (otherwise the forced tile is ignored for that bundle), block_size is 64, 128
- * or 256 (a kernel that sums norms takes the next size whose work-groups cover
- * 8 sites), tile_order is 0 (canonical site
- * order), 1 (a contiguous slab of tiles per XCD), 2 (per XCD, the time
+ * or 256, tile_order is 0 (canonical site order), 1 (a contiguous slab of tiles per XCD), 2 (per XCD, the time
  * slices of one slice position back to back; falls back to 1 where tiles
  * would straddle a time slice) or 3 (XCD j owns z-chunk j of L2/8 planes and
  * walks it x-y position outermost, then t, then z; falls back to 1 unless

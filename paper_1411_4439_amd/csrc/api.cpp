@@ -423,12 +423,8 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
         ford = eo ? g_force_eo_order : g_force_order;
         frows = eo ? g_force_eo_rows : g_force_rows;
     }
-    // a reducing kernel's work-group covers at least kLeastSites sites
-    auto enough = [&](const Tile& c) { return epi == EPI_PLAIN || tile_sites(lat, n, c) >= kLeastSites; };
     if (mode == 1 && valid_nr(n, fnr)) {
-        int sbs = staged_block(lat, n, n / fnr, frows, prec, epi);
-        if (sbs && !enough(Tile{fnr, sbs, 0, frows})) sbs = 0;
-        while (!enough(Tile{fnr, fbs, 0})) fbs *= 2;
+        const int sbs = staged_block(lat, n, n / fnr, frows, prec, epi);
         Tile t{fnr, sbs ? sbs : fbs, ford, sbs ? frows : 0};
         if (!t_order_ok(lat, n, t, t.remap)) t.remap = 1;
         *out = t;
@@ -458,11 +454,10 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
     std::vector<Trial> tried;
     for (int G = 1; G <= n; ++G) {
         if (n % G != 0) continue;
-        for (int bs : {64, 128, 256})
-            if (enough(Tile{n / G, bs, 0})) tried.push_back({0, Tile{n / G, bs, 1, 0}});
+        for (int bs : {64, 128, 256}) tried.push_back({0, Tile{n / G, bs, 1, 0}});
         for (int R = 2; R <= 16; ++R) {
             const int sbs = staged_block(lat, n, G, R, prec, epi);
-            if (sbs && enough(Tile{n / G, sbs, 0, R})) tried.push_back({0, Tile{n / G, sbs, 1, R}});
+            if (sbs) tried.push_back({0, Tile{n / G, sbs, 1, R}});
         }
     }
     if (cm && (epi == EPI_NORM || epi == EPI_CG) && small_launch(lat, n, 4)) {

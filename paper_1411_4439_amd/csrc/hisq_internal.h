@@ -115,18 +115,6 @@ __host__ __device__ inline size_t link_block_reals(int Vh, int nk)
     return size_t(144 + 8 * naik_reals(nk)) * size_t(Vh);
 }
 
-// FP32: position (in floats, from the slot's start) of real r (0 <= r < nr) of
-// site i's matrix.  Reals group into 16-byte words, [r/4][Vh][4], so that one
-// load brings two complex numbers; the nr % 4 remaining reals follow as a plane
-// [Vh][nr % 4].  FP64 slots are [element][Vh] complex.  Slot starts stay 16-byte
-// aligned because Vh is a multiple of 8.
-__host__ __device__ inline size_t slot_real_offset32(int r, int nr, int Vh, int i)
-{
-    const int nw = nr / 4, rem = nr % 4;
-    if (r < 4 * nw) return ((size_t)(r >> 2) * Vh + i) * 4 + (r & 3);
-    return (size_t)4 * nw * Vh + (size_t)i * rem + (r - 4 * nw);
-}
-
 // Per-rhs sums over a grid.  The kernel that produces a sum leaves at most
 // kSumDoubles / np rows of partial sums (np: the bundle size rounded up to a
 // power of two, the row's stride), and every wave of the kernel that needs the
@@ -291,8 +279,11 @@ inline int phase_of(int j) { return j == 0 ? 0 : (j & 1) ? 1 : 2; }
 // Reduction scratch for a grid of up to `blocks` work-groups: the rows of the
 // three sums of an iteration (|p|^2, |t|^2, |r|^2), then the partials.
 enum SumSlot { SUM_PP = 0, SUM_TT = 1, SUM_RR = 2, SUM_SLOTS = 3 };
-// Every reducing work-group covers at least kLeastSites sites and leaves at most two sums.
+// Every reducing work-group covers at least kLeastSites sites (whole waves, at most
+// kMaxRhs lanes per site; split_tile sees to it for four times that) and leaves at
+// most two sums.
 constexpr int kLeastSites = 8;
+static_assert(64 / kMaxRhs >= kLeastSites, "sites of a one-wave work-group");
 inline size_t red_doubles(int Vh, int n)
 {
     return (size_t)SUM_SLOTS * kSumDoubles + ((size_t)Vh / kLeastSites + 1) * 2 * sum_stride(n);

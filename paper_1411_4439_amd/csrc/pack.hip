@@ -107,8 +107,10 @@ __device__ __forceinline__ void encode(const d2 (&m)[9], double (&re)[18], float
     }
 }
 
-// Site i's NR reals of one slot (layout of slot_real_offset32 in FP32,
-// [element][Vh] complex in FP64), 16 bytes per store.
+// Site i's NR reals of one slot, 16 bytes per store.  FP32: reals group into 16-byte
+// words, [r / 4][Vh][4], so that one load brings two complex numbers; the NR % 4
+// remaining reals follow as a plane [Vh][NR % 4].  FP64: [element][Vh] complex.  Slot
+// starts stay 16-byte aligned because Vh is a multiple of 8.
 template <typename T, int NR>
 __device__ __forceinline__ void store_slot(T* slot, int Vh, int i, const double (&re)[18])
 {
