@@ -77,7 +77,7 @@ def parse():
                     help="skip the oracle's FP64 CG runs in the CPU baseline (the longest part)")
     ap.add_argument("--cpu-seconds", type=float, default=15.0)
     ap.add_argument("--tile", default=DEFAULT_TILE,
-                    help="tile of the solve's D_oe Dslash (and p-update): "
+                    help="tile of the solve's D_oe Dslash: "
                          "'rhs_per_thread,tile_order,stage_rows' (the autotuner's pick for this "
                          "workload, pinned so that every run and every counter profile times the "
                          "same kernels) or 'auto' (autotune both Dslash kernels)")

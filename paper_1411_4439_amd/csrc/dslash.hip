@@ -199,10 +199,9 @@ __device__ __forceinline__ void dslash_site(const Lat& lat, int P, int i, int g,
 // a site and its rhs tile, lane mu takes the four hops of direction mu, issues
 // all their loads at once and the quad adds the four partial results with DPP
 // permutes.  A wave then waits for one memory round trip instead of 16 in a
-// row, and there are four times as many waves.
-// 8^4, FP64, one rhs: a solve takes 2.87 ms on these kernels, 3.73 ms on the
-// sequential ones; where the sequential tiles fill the chip (from about 8 waves
-// per SIMD) four lanes only repeat the index arithmetic.
+// row, and there are four times as many waves; but every rhs loads its site's links
+// for itself.  Both sides, and where the line lies, stand with the launch rule
+// (kSplitLanes in api.cpp).
 template <typename T, int NK, int HH>
 __device__ __forceinline__ void load_link_dir(const cplx<T>* __restrict__ lk, int Vh, int i, int mu,
                                               cplx<T> (&m)[9])

@@ -109,8 +109,9 @@ __device__ __forceinline__ double wave_sum(double v)
 //            partial is the row and the kernel is done: no counter, no wait.
 //   stage 2 (sum_post, sum_finish): else the last work-group of each group of
 //            `group` (atomic counter) sums the group's partials into its row.
-//   stage 3 (sum_rows): the kernel that needs the sum adds the rows, in every
-//            wave.  The end of the producing kernel orders the rows before it.
+//   stage 3 (sum_rows): the kernel that needs the sum adds the rows: the p-update
+//            in every wave, D_eo in the first wave of each work-group.  The end of
+//            the producing kernel orders the rows before it.
 // A third stage inside the producer (the last group sums the group sums) cost
 // each reducing kernel 2-3 us of counter and load round trips at its end, and
 // counters in one cache line another 10 ns per work-group: together 5 us of a

@@ -117,8 +117,8 @@ __host__ __device__ inline size_t link_block_reals(int Vh, int nk)
 
 // Per-rhs sums over a grid.  The kernel that produces a sum leaves at most
 // kSumDoubles / np rows of partial sums (np: the bundle size rounded up to a
-// power of two, the row's stride), and every wave of the kernel that needs the
-// sum adds the rows itself: 8 loads per lane, no wait for a last work-group.
+// power of two, the row's stride), and the kernel that needs the sum adds the rows
+// itself, in every work-group: 8 loads per lane, no wait for a last work-group.
 // A grid of more work-groups than rows first sums groups of `sum_group`
 // consecutive work-groups into one row each.
 constexpr int kSumDoubles = 512;

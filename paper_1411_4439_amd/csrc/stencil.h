@@ -93,8 +93,9 @@ __device__ __forceinline__ void load_link(const cplx<T>* __restrict__ lk, int Vh
 // (word w to lane w mod G), each lane loads only its own, and when the slot is
 // used every lane gathers all words with DPP permutes inside its quad (a VALU
 // operation, no memory traffic).  The nr mod 4 trailing reals are one small
-// load per lane.  FP64 links keep one lane per load (their kernels run G <= 2
-// and use every register for the doubles).
+// load per lane.  FP64 links are not shared: every lane loads the whole matrix (the
+// doubles leave no registers for the exchange), which is why more lanes per site pay
+// in FP64 only where they bring waves that the chip lacks.
 template <typename T, int G>
 struct LinkRaw {
     static constexpr int kW = (4 + G - 1) / G;  // words per lane (<= 4 per slot)
