@@ -110,9 +110,9 @@ typedef struct {
 
 /* Kernel classes timed when hisq_params.profile = 1. */
 enum hisq_kclass {
-    HISQ_K_PUPDATE = 0,   /* p = r + beta p, |p|^2                           */
-    HISQ_K_DSLASH_OE = 1, /* t = D_oe p, |t|^2                               */
-    HISQ_K_DSLASH_EO = 2, /* D_eo t + CG epilogue: x, r updates, |r|^2       */
+    HISQ_K_PUPDATE = 0,   /* beta, masks, p = r + beta p                      */
+    HISQ_K_DSLASH_OE = 1, /* t = D_oe p, |p|^2, |t|^2                         */
+    HISQ_K_DSLASH_EO = 2, /* D_eo t + CG epilogue: alpha, x, r updates, |r|^2 */
     HISQ_K_RELIABLE = 3,  /* FP64 true residual (two FP64 half-Dslash + BLAS) */
     HISQ_K_FORCE = 4,     /* hisq_cg_solve_backward: the link-force kernel    */
     HISQ_K_COUNT = 5
@@ -301,8 +301,10 @@ int hisq_trace_estimate(const hisq_geom* g, double mass, int nrhs, const hisq_pa
 /*
  * Autotuner control (process-wide).  mode 0: time the candidate tiles on first
  * use of a (lattice, nrhs, precision, Naik, kernel) key and cache the fastest
- * (default); mode 1: always use rhs_per_thread / block_size / tile_order /
- * stage_rows;
+ * (default).  The first call of a shape pays for that: 2 to 11 ms for a half-Dslash
+ * up to 32^3 x 8, 8 to 39 ms at 48^3 x 12; 3 to 24 ms and 15 to 95 ms for a solve,
+ * which tunes two or three kernels.
+ * mode 1: always use rhs_per_thread / block_size / tile_order / stage_rows;
  * mode 2: built-in default, no timing.  rhs_per_thread must divide the bundle
  * (otherwise the forced tile is ignored for that bundle), block_size is 64, 128
  * or 256, tile_order is 0 (canonical site order), 1 (a contiguous slab of tiles per XCD), 2 (per XCD, the time
@@ -324,8 +326,9 @@ int hisq_set_tuning(int mode, int rhs_per_thread, int block_size, int tile_order
 /*
  * In a single solve the D_eo half-Dslash with the CG epilogue (it also reads
  * p, x, r and writes x, r) is tuned on its own, separately from D_oe, whose
- * tile the p-update, the batched kernels and the FP64 residual share; both
- * tiles are reported in hisq_info.  This call gives the D_eo kernel its own
+ * tile the FP64 residual shares; both tiles are reported in hisq_info.  (The
+ * p-update has a grid of its own, the batched kernels their own tuner.)  This
+ * call gives the D_eo kernel its own
  * tile under tuning mode 1, with the arguments of hisq_set_tuning; until it is
  * called, after rhs_per_thread = 0, and after every hisq_set_tuning call, that
  * kernel takes the mode-1 tile of hisq_set_tuning.  Returns HISQ_EINVAL for

@@ -4,8 +4,9 @@
 // The solver is the even-odd CG for A x = b with A = 4m^2 - D_eo D_oe and the
 // HISQ Dslash of Sec. 1 eq. (3), run on bundles of n rhs (eq. (4)); every rhs
 // has its own alpha, beta and convergence flag.  Per iteration three kernels
-// run: p = r + beta p (|p|^2), t = D_oe p (|t|^2, alpha), and
-// D_eo t fused with x += alpha p, r -= alpha (4m^2 p - D_eo t) (|r|^2, beta).
+// run: p = r + beta p (beta and the masks from the last |r|^2), t = D_oe p (sums
+// |p|^2 and |t|^2), and D_eo t fused with x += alpha p, r -= alpha (4m^2 p - D_eo t)
+// (alpha from |p|^2 and |t|^2; sums |r|^2).
 // alpha uses <p, A p> = 4m^2 |p|^2 + |D_oe p|^2, which holds because D is
 // anti-Hermitian (D_eo^dag = -D_oe).
 #include <hip/hip_runtime.h>
@@ -501,15 +502,15 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
         std::sort(v.begin(), v.end(), [](const Trial& x, const Trial& y) { return x.ms < y.ms; });
     };
     // A first call pays for this, so not every tile runs in every order.  Each runs in
-    // order 1 first (split tiles in 0); the best of them in the others; the first four
-    // of all three times more in turn.  A launch of 60 us and more is placed within a
-    // few percent by one run, and the six within 20% of the fastest go on.  Shorter ones
-    // find the caches as another tile left them: the eight within 30% run again, also
-    // in order 1, after an untimed launch.  Against every tile in every order, four
-    // launches each, and 72 of the first four (90 half-Dslashes and 60 solves, 12^3 x 6
-    // to 32^3 x 8): the tiles chosen are within 0.6% and 0.4% on average, which is the
-    // spread of either, and the choice takes 4 ms instead of 11 and 7.5 instead of 16.5;
-    // 25 instead of 180 for the half-Dslash at 48^3 x 12, FP64, n = 5.
+    // order 1 first (split tiles in 0); the best of them in all orders, each after an
+    // untimed launch (a tile's first launch finds the caches as another tile left them);
+    // the first four of these again in turn.  One launch places a long one (60 us and
+    // more) within a few percent, so four within 15% of the fastest go on there, and
+    // eight within 30% of the brief ones.  Against every tile in every order with four
+    // launches each, and 72 more of the first four (300 half-Dslashes and solves,
+    // 12^3 x 6 to 48^3 x 12): the tiles chosen are 1.4% and 0.4% faster on average, and
+    // a first half-Dslash takes 6 ms instead of 26 on average, at 48^3 x 12, FP64,
+    // n = 5 32 instead of 180.
     std::vector<Trial> builtin{{0, best}};
     int rc = time_all(builtin, 1, false);
     if (rc) return rc;
@@ -518,27 +519,22 @@ int get_tile(const Lat& lat, int n, int prec, int nk, const DslashArgs<T>& probe
     auto reps = [t0](float ms, int most) { return std::max(1, std::min(most, (int)(ms / t0))); };
     if ((rc = time_all(tried, reps(0.040f, 3), false))) return rc;
     fastest_first(tried);
-    size_t on = 0;
-    while (on < tried.size() && on < (brief ? 8u : 6u) && tried[on].ms <= (brief ? 1.3f : 1.2f) * tried[0].ms) ++on;
     std::vector<Trial> next;
-    for (size_t j = 0; j < on; ++j)
-        for (int order = 0; order < 4; ++order) {
-            Tile c = tried[j].t;
-            if ((order == c.remap && !brief) || !t_order_ok(lat, n, c, order)) continue;
-            c.remap = order;
-            next.push_back({0, c});
-        }
-    if (brief) tried.clear();
-    if ((rc = time_all(next, reps(0.120f, 3), brief))) return rc;
-    tried.insert(tried.end(), next.begin(), next.end());
-    fastest_first(tried);
-    if (tried.size() > 4) tried.resize(4);
-    std::vector<Trial> total = tried;
+    for (size_t j = 0; j < tried.size() && j < (brief ? 8u : 4u); ++j) {
+        Tile c = tried[j].t;
+        if (tried[j].ms > (brief ? 1.30f : 1.15f) * tried[0].ms) break;
+        for (c.remap = 0; c.remap < 4; ++c.remap)
+            if (t_order_ok(lat, n, c, c.remap)) next.push_back({0, c});
+    }
+    if ((rc = time_all(next, reps(0.120f, 3), true))) return rc;
+    fastest_first(next);
+    if (next.size() > 4) next.resize(4);
+    std::vector<Trial> total = next;
     for (Trial& t : total) t.ms = 0;
-    for (int round = 0; round < 3; ++round) {
-        if ((rc = time_all(tried, reps(0.150f, 6), brief))) return rc;
-        if (tried.size() != total.size()) return fail(HISQ_EHIP, "a launch of the autotuner failed");
-        for (size_t j = 0; j < tried.size(); ++j) total[j].ms += tried[j].ms;
+    for (int round = 0; round < (brief ? 3 : 2); ++round) {
+        if ((rc = time_all(next, reps(0.150f, 6), true))) return rc;
+        if (next.size() != total.size()) return fail(HISQ_EHIP, "a launch of the autotuner failed");
+        for (size_t j = 0; j < next.size(); ++j) total[j].ms += next[j].ms;
     }
     fastest_first(total);
     if (!total.empty()) best = total[0].t;
@@ -602,7 +598,7 @@ struct Prob {
     const d2* b = nullptr;  // colour-major working copies [3][Vh][n]
     d2* x = nullptr;
     Ws w;
-    Tile t64{}, t32{};    // D_oe with |t|^2 (tuned), the p-update, the FP64 residual
+    Tile t64{}, t32{};    // D_oe with |p|^2 and |t|^2 (tuned), the FP64 residual
     Tile t64e{}, t32e{};  // D_eo with the CG epilogue (tuned on its own)
     int bnr = 0;          // rhs per thread in the batched kernels (tuned with the batch)
     CgState* hs = nullptr;  // pinned host copy
@@ -632,8 +628,12 @@ struct Engine {
 
     // The one problem whose own kernels a poll block runs, or NULL: a single
     // solve's, or the last of a batch where one rhs per lane does not fill the
-    // chip (latency-bound launches: 158 iterations of 16^3 x 4, 3 rhs, at the end
-    // of six solves).
+    // chip (latency-bound launches, up to the lanes the autotuner tries split tiles
+    // for).  Batches of two with 160-200 iterations of the second alone, on the
+    // batched kernels / its own, ms, FP64 and mixed r14: 8^4 1 rhs 5.8 / 4.5, 5.9 / 5.2;
+    // 8 rhs 9.1 / 7.1, 8.8 / 7.7; 12^3 x 6 2 rhs 6.9 / 6.9, 7.2 / 6.8; 6 rhs (124k
+    // lanes) 9.8 / 8.8, 9.4 / 8.4; 16^3 x 4 3 rhs 10.5 / 9.5, 9.6 / 8.6; 4 rhs (131k)
+    // 10.7 / 9.3, 9.4 / 8.4.  Fixed tiles: a batch asks for no tile of one problem's own.
     const Prob* solo() const
     {
         if (P.size() == 1) return &P[0];

@@ -15,7 +15,7 @@ L = (32, 32, 24, 12)  # a shape that no other test has tuned
 @pytest.mark.parametrize("prec,n", [("f64", 5), ("f64", 8), ("r14", 7)])
 def test_first_call_of_a_shape(prec, n):
     """The tuner may take the time of 150 later calls, and 8 ms for loading kernels (it
-    takes about 60 and 3); every tile in every order took 250 to 550.  Its choice is no
+    takes 70 to 110 in all); every tile in every order took 250 to 550.  Its choice is no
     slower than the built-in tile."""
     import torch
     H = gpu_lib()
